@@ -149,8 +149,12 @@ void dsv_plan_free(dsv_plan* plan);
 
 /*
  * dsv_cobatch_fwd_workspace -- bytes of device workspace dsv_cobatch_fwd
- * needs for this plan, dtype and shape (h of every row, plus the fp32
- * low-rank terms of the gathered rows).
+ * needs for this plan, dtype and shape (h of every row, the fp32 low-rank
+ * terms of the gathered rows, and for batches of few rows the fp32 pieces of
+ * the base product).  A bf16 call whose workspace lacks only the room for the
+ * pieces takes whole tiles instead: slower, and Y (dX in the backward) may
+ * differ in the last bit (another summation order).  The same holds for the
+ * backward's and the grouped calls' workspaces.
  */
 int dsv_cobatch_fwd_workspace(const dsv_plan* plan, dsv_dtype dtype, int32_t K, int32_t N,
                               size_t* bytes);
@@ -179,9 +183,9 @@ int dsv_cobatch_fwd(const dsv_plan* plan, dsv_dtype dtype, int32_t K, int32_t N,
  * call on a device until the process ends.  The caller still passes inputs and
  * outputs; arguments, layouts and alignment as dsv_cobatch_fwd.
  * A batch whose intermediates exceed the scratch (dsv_cobatch_fwd_workspace of
- * the same plan and shape is an upper bound of what is used) returns
- * DSV_ERR_SIZE before any launch.  The base GEMM splits no tile along the
- * contraction (a split keeps a partial tile per piece): where
+ * the same plan and shape is an upper bound of what must fit) returns
+ * DSV_ERR_SIZE before any launch.  The base GEMM runs in pieces along the
+ * contraction where those fit the scratch, else in whole tiles: where
  * dsv_cobatch_fwd splits one (dsv_gemm_config pass 0 reports split tiles), Y
  * may differ from it in the last bit (another summation order); otherwise
  * Y and H_save are bit-identical to dsv_cobatch_fwd.
@@ -299,9 +303,9 @@ int dsv_lora_bwd_dropout(const dsv_plan* plan, dsv_dtype dtype, int32_t K, int32
  * it, with one launch per step for all projections instead of one per
  * projection: the rank-r kernels, token reductions and final sums run the
  * projections side by side, and the base GEMMs of all projections form one
- * launch of whole 256 x 256 tiles ordered by contraction length (longest
- * first), so one projection's last partial wave is filled by the next one's
- * tiles.  Operands may alias across entries (q/k/v read one X); outputs must
+ * launch: whole 256 x 256 tiles ordered by contraction length (longest first),
+ * so one projection's last partial wave is filled by the next one's tiles, or,
+ * for batches of few rows, pieces along the contraction.  Operands may alias across entries (q/k/v read one X); outputs must
  * not.  1 <= n_proj <= DSV_MAX_GROUP; n_proj = 1 is the single-projection
  * call.  Each entry follows the single call's shape, layout and alignment
  * rules; any entry that fails them fails the whole call before any launch.
@@ -492,7 +496,8 @@ int dsv_adamw_step_grouped(const dsv_plan* plan, dsv_dtype dtype, int32_t n_proj
  * device, for benchmarks and tests.  out[6] receives: tile rows, tile
  * columns, row tiles, column tiles, the number of tiles split along the
  * contraction and the number of pieces each of them is split into (0 and 0
- * when none is split).  The bf16 path picks, per launch, the tile shape and
+ * when none is split; every tile, with one piece or more, when the product runs
+ * in pieces that a second kernel sums).  The bf16 path picks, per launch, the tile shape and
  * split with the smallest estimated time; fp32 and empty passes report zeros.
  * Returns DSV_OK, DSV_ERR_ARG (NULL plan or out, pass not 0 or 1) or the
  * dsv_cobatch_fwd size and dtype errors. */

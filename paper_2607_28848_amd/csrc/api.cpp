@@ -87,6 +87,87 @@ GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool al
   return cost256 < cost128 ? p : best;
 }
 
+// GEMM in pieces (launch_part_gemm) for a batch's projections, or the tile
+// kernels above: both are costed in microseconds and the smaller cost wins.
+//   pieces   rounds of workgroups over the CUs times K-steps per piece times the
+//            configuration's time per step (at least the weights at 5.5 TB/s),
+//            plus the fp32 pieces written and read once each at 5 TB/s and the
+//            launch that sums them
+//   tiles    the 128 x 128 form's rounds at 1.0 us per K-step or the 256 x 256
+//            form's at 1.5 us (a split last round and its sum: 1/split of a round
+//            and the pieces' bytes); gathered rows cost another launch
+// Fitted to timings of M = 8 .. 2048 rows of the Llama-3-8B shapes on MI355X:
+// the pieces win below about 500 rows (M = 96, N = K = 4096: 19.0 against 32.5
+// us; M = 256, K = 14336: 50.9 against 59.3), the tiles above (M = 1500, K = N =
+// 4096: 57.9 against 71.0).
+struct PartPlan {
+  bool use = false;
+  int cfg = 0;
+  int32_t n_m[kMaxGroup] = {}, n_n[kMaxGroup] = {}, split[kMaxGroup] = {};
+  size_t off[kMaxGroup] = {}, bytes = 0;  // the pieces' buffers, past the rest of the workspace
+};
+constexpr int kMinPartSteps = 4;
+constexpr double kPartBytesPerUs = 5e6, kWeightBytesPerUs = 5.5e6, kSumUs = 4.0, kGatherUs = 6.0;
+
+double tiles_us(const GemmPlan& g, int32_t C) {
+  const int64_t cus = device_cus(), nk = (C + 63) / 64;
+  if (cus <= 0) return 0.0;  // no device: no launch plan either
+  if (g.tm == 128) return (double)((g.dp_tiles + 2 * cus - 1) / (2 * cus)) * nk * 1.0;
+  double t = (double)((g.dp_tiles + cus - 1) / cus) * nk * 1.5;
+  if (g.sk_tiles > 0)
+    t += 1.5 * nk / g.sk_split + kSumUs + (double)g.sk_tiles * g.sk_split * g.tm * g.tn * 8 / kPartBytesPerUs;
+  return t;
+}
+
+PartPlan part_plan(int32_t M, int32_t n, const int32_t* Nout, const int32_t* C, double t_tiles) {
+  PartPlan best;
+  const int cus = device_cus();
+  if (cus <= 0 || M <= 0) return best;
+  static const int kSplits[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
+  double w_us = 0, t_best = t_tiles - kSumUs;
+  int32_t nk[kMaxGroup], nk_max = 1;
+  for (int i = 0; i < n; ++i) {
+    nk[i] = (C[i] + 63) / 64;
+    w_us += 2.0 * Nout[i] * C[i] / kWeightBytesPerUs;
+    nk_max = std::max(nk_max, nk[i]);
+  }
+  if (w_us >= t_best) return best;
+  for (int cfg = 0; cfg < kPartCfgs; ++cfg) {
+    const PartCfg& pc = kPartCfg[cfg];
+    if (pc.tm < 64 && M > pc.tm) continue;  // the 32-row tile is for batches of one row tile
+    const int64_t slots = (int64_t)cus * pc.per_cu;
+    int32_t last = 0;
+    for (const int s : kSplits) {
+      const int32_t t = std::max((nk_max + s - 1) / s, std::min(kMinPartSteps, nk_max));
+      if (t == last) break;
+      last = t;
+      int64_t wgs = 0, elems = 0;
+      for (int i = 0; i < n; ++i) {
+        const int64_t sp = (nk[i] + t - 1) / t;
+        wgs += sp * ((M + pc.tm - 1) / pc.tm) * ((Nout[i] + pc.tn - 1) / pc.tn);
+        elems += sp * M * Nout[i];
+      }
+      if (wgs > INT32_MAX) break;
+      const double us = std::max((double)((wgs + slots - 1) / slots * t) * pc.step_us, w_us) +
+                        (double)elems * 8 / kPartBytesPerUs;
+      if (us < t_best) {
+        t_best = us;
+        best.use = true;
+        best.cfg = cfg;
+        for (int i = 0; i < n; ++i) best.split[i] = (nk[i] + t - 1) / t;
+      }
+    }
+  }
+  if (best.use)
+    for (int i = 0; i < n; ++i) {
+      best.n_m[i] = (M + kPartCfg[best.cfg].tm - 1) / kPartCfg[best.cfg].tm;
+      best.n_n[i] = (Nout[i] + kPartCfg[best.cfg].tn - 1) / kPartCfg[best.cfg].tn;
+      best.off[i] = best.bytes;
+      best.bytes += align256((size_t)best.split[i] * M * Nout[i] * 4);
+    }
+  return best;
+}
+
 struct FwdWs {
   size_t h_all, delta, keep, sk_part, rk_part, total;
 };
@@ -162,6 +243,49 @@ GemmPlan fwd_gemm_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N, bo
 GemmPlan bwd_gemm_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
   if (dt != DSV_BF16 || p.T_t == 0) return GemmPlan{};
   return plan_gemm(p.n_btiles, p.n_btiles128, K, N);
+}
+
+// Pieces or tiles of one projection's forward / dX GEMM.
+PartPlan fwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N, bool allow_split = true) {
+  if (dt != DSV_BF16 || p.T == 0) return PartPlan{};
+  return part_plan(p.T, 1, &N, &K, tiles_us(fwd_gemm_plan(p, dt, K, N, allow_split), K) + (p.n_gather > 0 ? kGatherUs : 0.0));
+}
+PartPlan bwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
+  if (dt != DSV_BF16 || p.T_t == 0) return PartPlan{};
+  return part_plan(p.T_t, 1, &K, &N, tiles_us(bwd_gemm_plan(p, dt, K, N), N));
+}
+// ... of a grouped call, whose tiles share one launch of whole 256 x 256 tiles.
+// A projection whose single call splits no contraction keeps its whole tiles
+// (its grouped result is the single call's, bit for bit).
+template <typename Proj, typename ShapeOf>
+PartPlan group_part_plan(const dsv_plan& p, int pass, int32_t n, const Proj* pr, ShapeOf shape) {
+  const int32_t M = pass == 0 ? p.T : p.T_t, mtiles = pass == 0 ? p.n_ftiles : p.n_btiles;
+  const int cus = device_cus();
+  if (cus <= 0 || M == 0) return PartPlan{};
+  int32_t Nout[DSV_MAX_GROUP], C[DSV_MAX_GROUP];
+  double steps = 0, longest = 0;
+  for (int i = 0; i < n; ++i) {
+    shape(pr[i], &Nout[i], &C[i]);
+    const double nk = (C[i] + 63) / 64;
+    steps += nk * mtiles * ((Nout[i] + 255) / 256);
+    longest = std::max(longest, nk);
+  }
+  // tiles in rounds over the CUs, the longest contraction setting the round
+  const double whole = std::ceil(steps / cus / longest) * longest * 1.5 + (pass == 0 && p.n_gather > 0 ? kGatherUs : 0.0);
+  const PartPlan pp = part_plan(M, n, Nout, C, whole);
+  for (int i = 0; pp.use && i < n; ++i)
+    if (!(pass == 0 ? fwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N) : bwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N)).sk_tiles &&
+        !(pass == 0 ? fwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N) : bwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N)).use)
+      return PartPlan{};
+  return pp;
+}
+PartPlan fwd_group_part(const dsv_plan& p, dsv_dtype dt, int32_t n, const dsv_fwd_proj* pr) {
+  if (dt != DSV_BF16) return PartPlan{};
+  return group_part_plan(p, 0, n, pr, [](const dsv_fwd_proj& q, int32_t* o, int32_t* c) { *o = q.N, *c = q.K; });
+}
+PartPlan bwd_group_part(const dsv_plan& p, dsv_dtype dt, int32_t n, const dsv_bwd_proj* pr) {
+  if (dt != DSV_BF16) return PartPlan{};
+  return group_part_plan(p, 1, n, pr, [](const dsv_bwd_proj& q, int32_t* o, int32_t* c) { *o = q.K, *c = q.N; });
 }
 
 int check_common(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N) {
@@ -384,6 +508,16 @@ extern "C" int dsv_gemm_config(const dsv_plan* p, dsv_dtype dt, int32_t K, int32
   if (!out || (pass != 0 && pass != 1)) return DSV_ERR_ARG;
   for (int i = 0; i < 6; ++i) out[i] = 0;
   if (dt != DSV_BF16 || (pass == 0 ? p->T : p->T_t) == 0) return DSV_OK;
+  const PartPlan pp = pass == 0 ? fwd_part_plan(*p, dt, K, N) : bwd_part_plan(*p, dt, K, N);
+  if (pp.use) {
+    out[0] = kPartCfg[pp.cfg].tm;
+    out[1] = kPartCfg[pp.cfg].tn;
+    out[2] = pp.n_m[0];
+    out[3] = pp.n_n[0];
+    out[4] = pp.n_m[0] * pp.n_n[0];
+    out[5] = pp.split[0];
+    return DSV_OK;
+  }
   const GemmPlan gp = pass == 0 ? fwd_gemm_plan(*p, dt, K, N) : bwd_gemm_plan(*p, dt, K, N);
   out[0] = gp.tm;
   out[1] = gp.tn;
@@ -399,7 +533,7 @@ extern "C" int dsv_cobatch_fwd_workspace(const dsv_plan* p, dsv_dtype dt, int32_
   int rc = check_common(p, dt, K, N);
   if (rc != DSV_OK) return rc;
   if (!bytes) return DSV_ERR_ARG;
-  *bytes = fwd_ws(*p, dt, K, N, fwd_gemm_plan(*p, dt, K, N)).total;
+  *bytes = fwd_ws(*p, dt, K, N, fwd_gemm_plan(*p, dt, K, N)).total + fwd_part_plan(*p, dt, K, N).bytes;
   return DSV_OK;
 }
 
@@ -408,7 +542,7 @@ extern "C" int dsv_lora_bwd_workspace(const dsv_plan* p, dsv_dtype dt, int32_t K
   int rc = check_common(p, dt, K, N);
   if (rc != DSV_OK) return rc;
   if (!bytes) return DSV_ERR_ARG;
-  *bytes = bwd_ws(*p, dt, K, N, bwd_gemm_plan(*p, dt, K, N)).total;
+  *bytes = bwd_ws(*p, dt, K, N, bwd_gemm_plan(*p, dt, K, N)).total + bwd_part_plan(*p, dt, K, N).bytes;
   return DSV_OK;
 }
 
@@ -417,7 +551,7 @@ extern "C" int dsv_lora_bwd_dropout_workspace(const dsv_plan* p, dsv_dtype dt, i
   int rc = check_common(p, dt, K, N);
   if (rc != DSV_OK) return rc;
   if (!bytes) return DSV_ERR_ARG;
-  *bytes = bwd_ws(*p, dt, K, N, bwd_gemm_plan(*p, dt, K, N)).total;
+  *bytes = bwd_ws(*p, dt, K, N, bwd_gemm_plan(*p, dt, K, N)).total + bwd_part_plan(*p, dt, K, N).bytes;
   return DSV_OK;
 }
 
@@ -440,6 +574,38 @@ bool mask_aligned(const dsv_dropout* d) { return !d || !d->mask || (reinterpret_
 // Where a projection's mask lives: the caller's buffer, else the workspace.
 uint32_t* mask_buffer(const dsv_dropout* d, void* ws_keep) {
   return d && d->mask ? d->mask : static_cast<uint32_t*>(ws_keep);
+}
+
+// The sum of the pieces over the forward's items / the backward's.
+FinishGroup fwd_finish(const dsv_plan& p) {
+  FinishGroup f{};
+  f.r_max = p.r_max;
+  f.items = p.dptr(p.lay.shrink_items);
+  f.rows = p.dptr(p.lay.shrink_rows);
+  f.ranks = p.dptr(p.lay.ranks);
+  f.scales = reinterpret_cast<const float*>(p.dptr(p.lay.scales));
+  return f;
+}
+FinishGroup bwd_finish(const dsv_plan& p) {
+  FinishGroup f{};
+  f.r_max = p.r_max;
+  f.items = p.dptr(p.lay.train_items);
+  f.ranks = p.dptr(p.lay.ranks);
+  return f;
+}
+// Appends projection i of the plan to the launch of the pieces and to their sum.
+void add_part(PartGroup& pg, FinishGroup& fg, const PartPlan& pp, int i, PartArgs a, char* parts, const uint16_t* L,
+              int64_t ldl, const void* Q, void* out, int64_t ldo, const uint32_t* keep, int32_t keep_words,
+              float keep_scale) {
+  a.n_m = pp.n_m[i];
+  a.n_n = pp.n_n[i];
+  a.split = pp.split[i];
+  a.part = reinterpret_cast<float*>(parts + pp.off[i]);
+  pg.a[pg.n] = a;
+  pg.off[pg.n + 1] = pg.off[pg.n] + a.n_m * a.n_n * a.split;
+  ++pg.n;
+  fg.a[fg.n++] = FinishArgs{a.part, a.split, a.M, a.Nout, L, ldl, static_cast<const uint16_t*>(Q),
+                            static_cast<uint16_t*>(out), ldo, keep, keep_words, keep_scale, 1};
 }
 
 // noalloc: the allocation-free form (dsv_cobatch_fwd_noalloc): the workspace is
@@ -537,6 +703,21 @@ int fwd_impl(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N, const void* 
   sk.r_max = p->r_max;
   sk.split_items = p->n_shrink;
   if ((e = launch_shrink(sk, p->n_shrink, p->r_used, s)) != hipSuccess) return DSV_ERR_DEVICE;
+
+  // 2a. few rows: the base product in pieces, then their sum with the low-rank
+  //     term of every row (a workspace without room for the pieces takes the tiles)
+  const PartPlan pp = fwd_part_plan(*p, dt, K, N, !noalloc);
+  if (pp.use && workspace_bytes >= ws.total && workspace_bytes - ws.total >= pp.bytes) {
+    PartGroup pg{};
+    FinishGroup fg = fwd_finish(*p);
+    add_part(pg, fg, pp, 0, PartArgs{static_cast<const uint16_t*>(X), ld.x, static_cast<const uint16_t*>(W), ld.w, p->T, N, K},
+             at<char>(workspace, ws.total), h_all, ldh, B, Y, ld.y, nullptr, 0, 1.f);
+    const int tk = noalloc ? -1 : timing_begin(0, s);
+    e = launch_part_gemm(pg, pp.cfg, false, s);
+    if (e == hipSuccess) e = launch_part_finish(fg, p->n_shrink, p->r_used, false, s);
+    timing_end(tk, s);
+    return e == hipSuccess ? DSV_OK : DSV_ERR_DEVICE;
+  }
 
   // 2. gathered rows: fp32 low-rank term, each touched adapter read once.
   if (p->n_gather > 0) {
@@ -801,7 +982,20 @@ int bwd_impl(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N, const void* 
   // 6. dx = dy W + g A_a on the matrix cores (W read with a transposing load).
   //    Under dropout g A_a passes through the input's mask (in the accumulators,
   //    between the low-rank prologue and the main loop).
+  const PartPlan pp = bwd_part_plan(*p, dt, K, N);
   auto dx_gemm = [&](hipStream_t s) -> int {
+    if (pp.use && workspace_bytes - ws.total >= pp.bytes) {  // few rows: in pieces, as in the forward
+      PartGroup pg{};
+      FinishGroup fg = bwd_finish(*p);
+      add_part(pg, fg, pp, 0, PartArgs{static_cast<const uint16_t*>(dY), ld.dy, static_cast<const uint16_t*>(Wt ? Wt : W),
+                                       Wt ? ld.wt : ld.w, p->T_t, K, N},
+               at<char>(workspace, ws.total), gm, ldh, A, dX, ld.dx, keep, keep_words, ds.scale);
+      const int tk = timing_begin(1, s);
+      hipError_t e = launch_part_gemm(pg, pp.cfg, Wt == nullptr, s);
+      if (e == hipSuccess) e = launch_part_finish(fg, p->n_titems, p->r_train, true, s);
+      timing_end(tk, s);
+      return e == hipSuccess ? DSV_OK : DSV_ERR_DEVICE;
+    }
     GemmArgs g{};
     g.P = static_cast<const uint16_t*>(dY);
     g.ldp = ld.dy;
@@ -960,7 +1154,7 @@ extern "C" int dsv_cobatch_fwd_grouped_workspace(const dsv_plan* p, dsv_dtype dt
     if ((rc = check_common(p, dt, projs[i].K, projs[i].N)) != DSV_OK) return rc;
   size_t base[DSV_MAX_GROUP];
   FwdWs w[DSV_MAX_GROUP];
-  *bytes = fwd_group_ws(*p, dt, n_proj, projs, base, w);
+  *bytes = fwd_group_ws(*p, dt, n_proj, projs, base, w) + fwd_group_part(*p, dt, n_proj, projs).bytes;
   return DSV_OK;
 }
 
@@ -974,7 +1168,7 @@ extern "C" int dsv_lora_bwd_grouped_workspace(const dsv_plan* p, dsv_dtype dt, i
     if ((rc = check_common(p, dt, projs[i].K, projs[i].N)) != DSV_OK) return rc;
   size_t base[DSV_MAX_GROUP];
   BwdWs w[DSV_MAX_GROUP];
-  *bytes = bwd_group_ws(*p, dt, n_proj, projs, base, w);
+  *bytes = bwd_group_ws(*p, dt, n_proj, projs, base, w) + bwd_group_part(*p, dt, n_proj, projs).bytes;
   return DSV_OK;
 }
 
@@ -1091,6 +1285,24 @@ int fwd_grouped_impl(const dsv_plan* p, dsv_dtype dt, int32_t n_proj, const dsv_
     }
   }
   if (launch_shrink_group(sg, p->n_shrink, p->r_used, s) != hipSuccess) return DSV_ERR_DEVICE;
+
+  // 2a. few rows: every base product in pieces, then their sums with the low-rank terms
+  const PartPlan pp = fwd_group_part(*p, dt, n_proj, projs);
+  if (pp.use && workspace_bytes - total >= pp.bytes) {
+    PartGroup pg{};
+    FinishGroup fg = fwd_finish(*p);
+    for (int i = 0; i < n_proj; ++i) {
+      const dsv_fwd_proj& q = projs[i];
+      add_part(pg, fg, pp, i, PartArgs{static_cast<const uint16_t*>(q.X), st[i].x, static_cast<const uint16_t*>(q.W),
+                                       st[i].w, p->T, q.N, q.K},
+               wsb + total, sg.a[i].out1, ldh, q.B, q.Y, st[i].y, nullptr, 0, 1.f);
+    }
+    const int tk = timing_begin(0, s);
+    hipError_t e = launch_part_gemm(pg, pp.cfg, false, s);
+    if (e == hipSuccess) e = launch_part_finish(fg, p->n_shrink, p->r_used, false, s);
+    timing_end(tk, s);
+    return e == hipSuccess ? DSV_OK : DSV_ERR_DEVICE;
+  }
 
   // 2. gathered rows of every projection in one launch
   if (p->n_gather > 0) {
@@ -1332,7 +1544,28 @@ int bwd_grouped_impl(const dsv_plan* p, dsv_dtype dt, int32_t n_proj, const dsv_
 
   // 6. every dX GEMM in one launch, longest contraction first (projections with a
   //    transposed weight in one NT launch, the others in one NN launch)
+  const PartPlan pp = bwd_group_part(*p, dt, n_proj, projs);
   auto dx_all = [&](hipStream_t s) -> int {
+    if (pp.use && workspace_bytes - total >= pp.bytes) {  // few rows: in pieces, one sum for all
+      FinishGroup fg = bwd_finish(*p);
+      const int tk = timing_begin(1, s);
+      hipError_t e = hipSuccess;
+      for (int nt = 1; nt >= 0 && e == hipSuccess; --nt) {
+        PartGroup pg{};
+        for (int i = 0; i < n_proj; ++i) {
+          const dsv_bwd_proj& q = projs[i];
+          if (!q.dX || (q.Wt != nullptr) != (nt == 1)) continue;
+          add_part(pg, fg, pp, i, PartArgs{static_cast<const uint16_t*>(q.dY), st[i].dy,
+                                           static_cast<const uint16_t*>(nt ? q.Wt : q.W), nt ? st[i].wt : st[i].w,
+                                           p->T_t, q.K, q.N},
+                   wsb + total, gm[i], ldh, q.A, q.dX, st[i].dx, keep[i], (q.K + 31) / 32, ds[i].scale);
+        }
+        if (pg.n > 0) e = launch_part_gemm(pg, pp.cfg, nt == 0, s);
+      }
+      if (fg.n > 0 && e == hipSuccess) e = launch_part_finish(fg, p->n_titems, p->r_train, true, s);
+      timing_end(tk, s);
+      return e == hipSuccess ? DSV_OK : DSV_ERR_DEVICE;
+    }
     int32_t Cs[DSV_MAX_GROUP], order[DSV_MAX_GROUP];
     for (int i = 0; i < n_proj; ++i) Cs[i] = projs[i].N;
     by_contraction(n_proj, Cs, order);

@@ -1345,6 +1345,17 @@ void set_launch_events(hipEvent_t start, hipEvent_t stop) {
   g_ev_stop = stop;
 }
 
+hipEvent_t take_launch_start() {
+  hipEvent_t e = g_ev_start;
+  g_ev_start = nullptr;
+  return e;
+}
+hipEvent_t take_launch_stop() {
+  hipEvent_t e = g_ev_stop;
+  g_ev_stop = nullptr;
+  return e;
+}
+
 bool launch_events_pending() { return g_ev_start != nullptr || g_ev_stop != nullptr; }
 
 hipError_t launch_gemm_nn(const GemmArgs& a, int tm, int tn, hipStream_t s) {

@@ -182,6 +182,58 @@ struct GemmGroup {
   int32_t n;
 };
 
+// GEMM in pieces along the contraction, for batches whose 256 x 256 tiles leave
+// most of the chip idle.  One projection: tiles of the configuration's size over
+// [M][Nout], each tile's contraction cut into `split` pieces of whole 64-wide
+// K-steps; piece q writes its fp32 product to part[q][M][Nout].
+struct PartArgs {
+  const uint16_t* P;
+  int64_t ldp;
+  const uint16_t* Q;     // NT: [Nout][C], NN: [C][Nout]
+  int64_t ldq;
+  int32_t M, Nout, C;
+  int32_t n_m, n_n, split;
+  float* part;
+};
+// Configurations: tile, threads, workgroups per CU (by LDS), and the time of one
+// 64-wide K-step of a workgroup with every CU busy (microseconds, measured on
+// MI355X), from which the launch plan is costed.
+struct PartCfg {
+  int tm, tn, threads, per_cu;
+  double step_us;
+};
+constexpr int kPartCfgs = 4;
+constexpr PartCfg kPartCfg[kPartCfgs] = {
+    {32, 64, 256, 3, 0.25}, {64, 128, 512, 1, 0.33}, {128, 128, 512, 1, 0.5}, {128, 256, 512, 1, 0.85}};
+struct PartGroup {
+  PartArgs a[kMaxGroup];
+  int32_t off[kMaxGroup + 1];  // workgroups [off[p], off[p + 1]) run projection p
+  int32_t n;
+};
+// The sum of a projection's pieces plus the low-rank term of every row.
+struct FinishArgs {
+  const float* part;
+  int32_t split, M, Nout;
+  const uint16_t* L;     // h of every token row (forward), g of the compact training rows (backward)
+  int64_t ldl;
+  const uint16_t* Q;     // B [n_ad][Nout][r_max] (forward), A [n_ad][r_max][Nout] (backward)
+  uint16_t* out;
+  int64_t ldo;
+  const uint32_t* keep;  // backward: dropout mask of the low-rank term (nullptr: none)
+  int32_t keep_words;
+  float keep_scale;
+  int32_t iters;         // set by the launcher: 256-column blocks per workgroup
+};
+struct FinishGroup {
+  FinishArgs a[kMaxGroup];
+  int32_t yoff[kMaxGroup + 1];  // set by the launcher: prefix of the workgroup rows
+  int32_t n, r_max;
+  const int32_t* items;  // {adapter, begin, count, aux}: <= 32 rows (forward), <= 16 (backward)
+  const int32_t* rows;   // forward: item element -> token row; backward: nullptr (compact rows)
+  const int32_t* ranks;
+  const float* scales;   // nullptr: scale 1
+};
+
 // Device scratch of the allocation-free forward (dsv_cobatch_fwd_noalloc): a
 // file-scope array of kNoAllocScratchBytes in the library's device memory,
 // one copy per device.  noalloc_scratch() returns the current device's address
@@ -201,6 +253,12 @@ hipError_t launch_gemm_nt(const GemmArgs& a, int tm, int tn, hipStream_t s);
 void set_launch_events(hipEvent_t start, hipEvent_t stop);
 bool launch_events_pending();
 hipError_t launch_gemm_nn(const GemmArgs& a, int tm, int tn, hipStream_t s);
+// The pending events, handed over to a launch outside gemm_bf16.hip (nullptr: none).
+hipEvent_t take_launch_start();
+hipEvent_t take_launch_stop();
+// The pieces' kernel in configuration cfg (kPartCfg), and the sum of the pieces.
+hipError_t launch_part_gemm(const PartGroup& g, int cfg, bool nn, hipStream_t s);
+hipError_t launch_part_finish(FinishGroup g, int32_t n_items, int32_t r_sel, bool bwd, hipStream_t s);
 // Rank-r contractions: r_sel bounds the rank of every item's adapter (it sizes
 // the rank tiles); the partials of a split contraction have stride a.r_max.
 hipError_t launch_shrink(const SkinnyArgs& a, int32_t n_items, int32_t r_sel, hipStream_t s);

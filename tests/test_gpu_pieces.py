@@ -1,0 +1,112 @@
+"""GPU parity of the base products that run in pieces along the contraction (batches of
+few rows) and of the tile kernels that take over when the workspace has no room for the
+pieces: rows, columns and contractions around the edges of the tiles (32 / 64 / 128 rows,
+64 / 128 columns, 64-wide K-steps), ranks whose rows are and are not 16-byte aligned,
+single and grouped calls, W as it is and transposed, with and without dropout.
+
+Bar: 2e-2 against the fp64 reference (bf16 inputs, fp32 sums, one rounding), and a
+repeated call is bit-identical.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2607_28848_amd import workloads as wl
+from gpu_util import TOL_BF16, oracle_bwd, oracle_fwd, to_dev, to_host, train_mask_slices
+
+pytestmark = pytest.mark.gpu
+
+
+def _bits(t):
+    import torch
+    return t.view(torch.int16) if t.dtype == torch.bfloat16 else t.view(torch.int32)
+
+
+def _segments(T, Tt, n_ad):
+    """Decode rows, one prefill segment and a training segment split over two adapters."""
+    segs, pos = [], 0
+    n_dec = min(T - Tt, 5)
+    for i in range(n_dec):
+        segs.append((pos, 1, i % n_ad, 0))
+        pos += 1
+    if Tt:
+        cut = max(1, Tt * 2 // 3)
+        segs.append((pos, cut, 1 % n_ad, 1))
+        pos += cut
+        if Tt - cut:
+            segs.append((pos, Tt - cut, 2 % n_ad, 1))
+            pos += Tt - cut
+    if T - pos:
+        segs.append((pos, T - pos, 0, 0))
+    return segs
+
+
+CASES = [
+    # T, T_t, K, N, r_max, ranks
+    (1, 0, 1032, 72, 64, [16, 8, 64]),        # one decode row; K = 16 steps + 8, one ragged column tile
+    (32, 0, 2056, 264, 16, [16, 8, 5]),       # a full 32-row tile
+    (33, 20, 2048, 1000, 12, [12, 8, 5]),     # one row past it; rank rows of 24 bytes
+    (65, 33, 4096, 1160, 64, [64, 33, 16]),   # one row past the 64-row tile, both rank steps
+    (129, 64, 1544, 2056, 32, [32, 16, 7]),
+    (260, 129, 2056, 1288, 16, [16, 8, 16]),  # several items and row tiles
+]
+
+
+@pytest.mark.parametrize("wt", [False, True])
+@pytest.mark.parametrize("T,Tt,K,N,r_max,ranks", CASES)
+def test_pieces_and_tiles_against_reference(T, Tt, K, N, r_max, ranks, wt):
+    import torch
+    from paper_2607_28848_amd import dsv
+    w = wl.custom(_segments(T, Tt, len(ranks)), ranks, K=K, N=N, r_max=r_max, name="pieces")
+    shapes = [(K, N), (K, 2 * N)]  # a group of two on the same batch
+    w.projections = [wl.Projection("p%d" % i, *s) for i, s in enumerate(shapes)]
+    ts = [w.tensors(i, pad=np.nan) for i in range(2)]
+    dev = [{k: to_dev(t.store[k], "bf16") for k in ("X", "W", "A", "B", "dY")} for t in ts]
+    plan = dsv.segments_build(w.segments, w.n_tokens, w.ranks, w.scales, w.r_max, device="cuda")
+    drops = [(0.1, 5, 1), (0.1, 5, 2)] if wt and Tt else None
+    keep = [oracle.dropout_multipliers(Tt, k, *drops[i]) if drops else None for i, (k, _) in enumerate(shapes)]
+    refs = []
+    for i in range(2):
+        w.projections = [wl.Projection("p", *shapes[i])]
+        Yr, _ = oracle_fwd(w, ts[i], drop=keep[i])
+        refs.append((Yr, oracle_bwd(w, ts[i], drop=keep[i]) if Tt else None))
+
+    def run(ids, short):
+        """Grouped forward and backward of projections ids; short: workspaces 256 bytes too
+        small for the pieces, so the tile kernels run."""
+        sh = [shapes[i] for i in ids]
+        need = [dsv.fwd_grouped_workspace_bytes(plan, dsv.BF16, sh)]
+        need += [dsv.bwd_grouped_workspace_bytes(plan, dsv.BF16, sh)] if Tt else []
+        ws = [torch.empty(n - (256 if short else 0), dtype=torch.uint8, device="cuda") for n in need]
+        dr = [drops[i] for i in ids] if drops else None
+        out = dsv.cobatch_fwd_grouped(plan, [(dev[i]["X"], dev[i]["W"], dev[i]["A"], dev[i]["B"]) for i in ids],
+                                      workspace=ws[0], dropouts=dr)
+        grads = dsv.lora_bwd_grouped(
+            plan, [(dev[i]["X"], dev[i]["W"], dev[i]["A"], dev[i]["B"], out[n][1], dev[i]["dY"])
+                   for n, i in enumerate(ids)], workspace=ws[1], dropouts=dr,
+            wts=[dev[i]["W"].t().contiguous() for i in ids] if wt else None) if Tt else []
+        torch.cuda.synchronize()
+        return out, grads
+
+    fc = dsv.gemm_config(plan, dsv.BF16, K, N, 0)
+    print("T=%d T_t=%d K=%d N=%d wt=%s: fwd %s" % (T, Tt, K, N, wt, fc), flush=True)
+    # pieces are what is tested: every tile summed from pieces
+    assert fc["split_tiles"] == fc["row_tiles"] * fc["col_tiles"] > 0
+    for ids in ([0], [0, 1]):
+        for short in (False, True):
+            out, grads = run(ids, short)
+            out2, grads2 = run(ids, short)
+            for n, i in enumerate(ids):
+                errs = {"Y": oracle.rel_err(to_host(out[n][0]), refs[i][0])}
+                assert torch.equal(_bits(out[n][0]), _bits(out2[n][0]))
+                if Tt:
+                    _, dAr, dBr, dXr = refs[i][1]
+                    errs["dX"] = oracle.rel_err(to_host(grads[n][2]), dXr)
+                    assert torch.equal(_bits(grads[n][2]), _bits(grads2[n][2]))
+                    dA, dB = to_host(grads[n][0]), to_host(grads[n][1])
+                    for a, r in train_mask_slices(w):
+                        errs["dA%d" % a] = oracle.rel_err(dA[a, :r], dAr[a, :r])
+                        errs["dB%d" % a] = oracle.rel_err(dB[a, :, :r], dBr[a, :, :r])
+                print("  ids %s short %s " % (ids, short) + ", ".join("%s=%.1e" % kv for kv in errs.items()), flush=True)
+                for k, v in errs.items():
+                    assert v <= TOL_BF16, (ids, short, k, v)
