@@ -105,6 +105,7 @@ struct PartPlan {
   int cfg = 0;
   int32_t n_m[kMaxGroup] = {}, n_n[kMaxGroup] = {}, split[kMaxGroup] = {};
   size_t off[kMaxGroup] = {}, bytes = 0;  // the pieces' buffers, past the rest of the workspace
+  size_t h_off[kMaxGroup] = {};           // forward: the shrink's pieces
 };
 constexpr int kMinPartSteps = 4;
 constexpr double kPartBytesPerUs = 5e6, kWeightBytesPerUs = 5.5e6, kSumUs = 4.0, kGatherUs = 6.0;
@@ -119,7 +120,8 @@ double tiles_us(const GemmPlan& g, int32_t C) {
   return t;
 }
 
-PartPlan part_plan(int32_t M, int32_t n, const int32_t* Nout, const int32_t* C, double t_tiles) {
+// p (forward): the plan whose shrink runs beside the pieces.
+PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout, const int32_t* C, double t_tiles) {
   PartPlan best;
   const int cus = device_cus();
   if (cus <= 0 || M <= 0) return best;
@@ -164,6 +166,11 @@ PartPlan part_plan(int32_t M, int32_t n, const int32_t* Nout, const int32_t* C, 
       best.n_n[i] = (Nout[i] + kPartCfg[best.cfg].tn - 1) / kPartCfg[best.cfg].tn;
       best.off[i] = best.bytes;
       best.bytes += align256((size_t)best.split[i] * M * Nout[i] * 4);
+      if (!p) continue;
+      int32_t pieces, cpp;
+      skinny_split(C[i], p->n_shrink, &pieces, &cpp);
+      best.h_off[i] = best.bytes;
+      best.bytes += align256((size_t)pieces * M * p->r_max * 4);
     }
   return best;
 }
@@ -248,11 +255,11 @@ GemmPlan bwd_gemm_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
 // Pieces or tiles of one projection's forward / dX GEMM.
 PartPlan fwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N, bool allow_split = true) {
   if (dt != DSV_BF16 || p.T == 0) return PartPlan{};
-  return part_plan(p.T, 1, &N, &K, tiles_us(fwd_gemm_plan(p, dt, K, N, allow_split), K) + (p.n_gather > 0 ? kGatherUs : 0.0));
+  return part_plan(&p, p.T, 1, &N, &K, tiles_us(fwd_gemm_plan(p, dt, K, N, allow_split), K) + (p.n_gather > 0 ? kGatherUs : 0.0));
 }
 PartPlan bwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
   if (dt != DSV_BF16 || p.T_t == 0) return PartPlan{};
-  return part_plan(p.T_t, 1, &K, &N, tiles_us(bwd_gemm_plan(p, dt, K, N), N));
+  return part_plan(nullptr, p.T_t, 1, &K, &N, tiles_us(bwd_gemm_plan(p, dt, K, N), N));
 }
 // ... of a grouped call, whose tiles share one launch of whole 256 x 256 tiles.
 // A projection whose single call splits no contraction keeps its whole tiles
@@ -272,7 +279,7 @@ PartPlan group_part_plan(const dsv_plan& p, int pass, int32_t n, const Proj* pr,
   }
   // tiles in rounds over the CUs, the longest contraction setting the round
   const double whole = std::ceil(steps / cus / longest) * longest * 1.5 + (pass == 0 && p.n_gather > 0 ? kGatherUs : 0.0);
-  const PartPlan pp = part_plan(M, n, Nout, C, whole);
+  const PartPlan pp = part_plan(pass == 0 ? &p : nullptr, M, n, Nout, C, whole);
   for (int i = 0; pp.use && i < n; ++i)
     if (!(pass == 0 ? fwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N) : bwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N)).sk_tiles &&
         !(pass == 0 ? fwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N) : bwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N)).use)
@@ -579,6 +586,7 @@ uint32_t* mask_buffer(const dsv_dropout* d, void* ws_keep) {
 // The sum of the pieces over the forward's items / the backward's.
 FinishGroup fwd_finish(const dsv_plan& p) {
   FinishGroup f{};
+  f.row_train = p.dptr(p.lay.row_train);
   f.r_max = p.r_max;
   f.items = p.dptr(p.lay.shrink_items);
   f.rows = p.dptr(p.lay.shrink_rows);
@@ -604,8 +612,32 @@ void add_part(PartGroup& pg, FinishGroup& fg, const PartPlan& pp, int i, PartArg
   pg.a[pg.n] = a;
   pg.off[pg.n + 1] = pg.off[pg.n] + a.n_m * a.n_n * a.split;
   ++pg.n;
-  fg.a[fg.n++] = FinishArgs{a.part, a.split, a.M, a.Nout, L, ldl, static_cast<const uint16_t*>(Q),
+  fg.a[fg.n++] = FinishArgs{a.part, a.split, a.M, a.Nout, L, ldl, nullptr, 0, nullptr, static_cast<const uint16_t*>(Q),
                             static_cast<uint16_t*>(out), ldo, keep, keep_words, keep_scale, 1};
+}
+// Puts the shrink of the last appended projection (i of the plan) beside its
+// pieces; its h then reaches the sum as pieces.
+void add_part_shrink(const dsv_plan& p, PartGroup& pg, FinishGroup& fg, const PartPlan& pp, int i, const void* A,
+                     char* parts, void* H_save) {
+  const PartArgs& a = pg.a[pg.n - 1];
+  PartShrink& h = pg.sh[pg.n - 1];
+  h.X = a.P;
+  h.ldx = a.ldp;
+  h.A = static_cast<const uint16_t*>(A);
+  h.C = a.C;
+  h.part = reinterpret_cast<float*>(parts + pp.h_off[i]);
+  skinny_split(a.C, p.n_shrink, &h.pieces, &h.cpp);
+  pg.sh_off[pg.n] = pg.sh_off[pg.n - 1] + p.n_shrink * h.pieces;
+  pg.items = p.dptr(p.lay.shrink_items);
+  pg.rows = p.dptr(p.lay.shrink_rows);
+  pg.ranks = p.dptr(p.lay.ranks);
+  pg.n_items = p.n_shrink;
+  pg.T = p.T;
+  pg.r_max = p.r_max;
+  FinishArgs& f = fg.a[fg.n - 1];
+  f.h_part = h.part;
+  f.h_pieces = h.pieces;
+  f.h_save = p.T_t > 0 ? static_cast<uint16_t*>(H_save) : nullptr;
 }
 
 // noalloc: the allocation-free form (dsv_cobatch_fwd_noalloc): the workspace is
@@ -702,22 +734,25 @@ int fwd_impl(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N, const void* 
   sk.part_n = p->T;
   sk.r_max = p->r_max;
   sk.split_items = p->n_shrink;
-  if ((e = launch_shrink(sk, p->n_shrink, p->r_used, s)) != hipSuccess) return DSV_ERR_DEVICE;
-
-  // 2a. few rows: the base product in pieces, then their sum with the low-rank
-  //     term of every row (a workspace without room for the pieces takes the tiles)
+  // 1a. few rows: the base product in pieces, the shrink beside them (a launch of
+  //     its own where dropout masks it), then their sum with the low-rank term of
+  //     every row.  A workspace without room for the pieces takes the tiles.
   const PartPlan pp = fwd_part_plan(*p, dt, K, N, !noalloc);
-  if (pp.use && workspace_bytes >= ws.total && workspace_bytes - ws.total >= pp.bytes) {
+  const bool pieces = pp.use && workspace_bytes >= ws.total && workspace_bytes - ws.total >= pp.bytes;
+  if (pieces) {
+    if (keep && launch_shrink(sk, p->n_shrink, p->r_used, s) != hipSuccess) return DSV_ERR_DEVICE;
     PartGroup pg{};
     FinishGroup fg = fwd_finish(*p);
     add_part(pg, fg, pp, 0, PartArgs{static_cast<const uint16_t*>(X), ld.x, static_cast<const uint16_t*>(W), ld.w, p->T, N, K},
              at<char>(workspace, ws.total), h_all, ldh, B, Y, ld.y, nullptr, 0, 1.f);
+    if (!keep) add_part_shrink(*p, pg, fg, pp, 0, A, at<char>(workspace, ws.total), H_save);
     const int tk = noalloc ? -1 : timing_begin(0, s);
-    e = launch_part_gemm(pg, pp.cfg, false, s);
+    e = launch_part_gemm(pg, pp.cfg, p->r_used, false, s);
     if (e == hipSuccess) e = launch_part_finish(fg, p->n_shrink, p->r_used, false, s);
     timing_end(tk, s);
     return e == hipSuccess ? DSV_OK : DSV_ERR_DEVICE;
   }
+  if ((e = launch_shrink(sk, p->n_shrink, p->r_used, s)) != hipSuccess) return DSV_ERR_DEVICE;
 
   // 2. gathered rows: fp32 low-rank term, each touched adapter read once.
   if (p->n_gather > 0) {
@@ -991,7 +1026,7 @@ int bwd_impl(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N, const void* 
                                        Wt ? ld.wt : ld.w, p->T_t, K, N},
                at<char>(workspace, ws.total), gm, ldh, A, dX, ld.dx, keep, keep_words, ds.scale);
       const int tk = timing_begin(1, s);
-      hipError_t e = launch_part_gemm(pg, pp.cfg, Wt == nullptr, s);
+      hipError_t e = launch_part_gemm(pg, pp.cfg, p->r_train, Wt == nullptr, s);
       if (e == hipSuccess) e = launch_part_finish(fg, p->n_titems, p->r_train, true, s);
       timing_end(tk, s);
       return e == hipSuccess ? DSV_OK : DSV_ERR_DEVICE;
@@ -1284,11 +1319,11 @@ int fwd_grouped_impl(const dsv_plan* p, dsv_dtype dt, int32_t n_proj, const dsv_
       sk.drop_scale = ds[i].scale;
     }
   }
-  if (launch_shrink_group(sg, p->n_shrink, p->r_used, s) != hipSuccess) return DSV_ERR_DEVICE;
-
-  // 2a. few rows: every base product in pieces, then their sums with the low-rank terms
+  // 1a. few rows: every base product in pieces, the shrinks beside them (a launch
+  //     of their own where dropout masks them), then their sums with the low-rank terms
   const PartPlan pp = fwd_group_part(*p, dt, n_proj, projs);
   if (pp.use && workspace_bytes - total >= pp.bytes) {
+    if (dropping && launch_shrink_group(sg, p->n_shrink, p->r_used, s) != hipSuccess) return DSV_ERR_DEVICE;
     PartGroup pg{};
     FinishGroup fg = fwd_finish(*p);
     for (int i = 0; i < n_proj; ++i) {
@@ -1296,13 +1331,15 @@ int fwd_grouped_impl(const dsv_plan* p, dsv_dtype dt, int32_t n_proj, const dsv_
       add_part(pg, fg, pp, i, PartArgs{static_cast<const uint16_t*>(q.X), st[i].x, static_cast<const uint16_t*>(q.W),
                                        st[i].w, p->T, q.N, q.K},
                wsb + total, sg.a[i].out1, ldh, q.B, q.Y, st[i].y, nullptr, 0, 1.f);
+      if (!dropping) add_part_shrink(*p, pg, fg, pp, i, q.A, wsb + total, q.H_save);
     }
     const int tk = timing_begin(0, s);
-    hipError_t e = launch_part_gemm(pg, pp.cfg, false, s);
+    hipError_t e = launch_part_gemm(pg, pp.cfg, p->r_used, false, s);
     if (e == hipSuccess) e = launch_part_finish(fg, p->n_shrink, p->r_used, false, s);
     timing_end(tk, s);
     return e == hipSuccess ? DSV_OK : DSV_ERR_DEVICE;
   }
+  if (launch_shrink_group(sg, p->n_shrink, p->r_used, s) != hipSuccess) return DSV_ERR_DEVICE;
 
   // 2. gathered rows of every projection in one launch
   if (p->n_gather > 0) {
@@ -1560,7 +1597,7 @@ int bwd_grouped_impl(const dsv_plan* p, dsv_dtype dt, int32_t n_proj, const dsv_
                                            p->T_t, q.K, q.N},
                    wsb + total, gm[i], ldh, q.A, q.dX, st[i].dx, keep[i], (q.K + 31) / 32, ds[i].scale);
         }
-        if (pg.n > 0) e = launch_part_gemm(pg, pp.cfg, nt == 0, s);
+        if (pg.n > 0) e = launch_part_gemm(pg, pp.cfg, p->r_train, nt == 0, s);
       }
       if (fg.n > 0 && e == hipSuccess) e = launch_part_finish(fg, p->n_titems, p->r_train, true, s);
       timing_end(tk, s);

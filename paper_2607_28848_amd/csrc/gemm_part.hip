@@ -38,9 +38,107 @@ __device__ __forceinline__ i32x4 part_rsrc(const void* base, int64_t bytes) {
 }
 
 template <int V>
-struct stage_c {
+struct stage_c {  // a compile-time number passed as a value
   static constexpr int value = V;
 };
+
+// ---------------------------------------------------------------------------
+// Shrink of one item (<= 32 rows of one adapter) over one piece of the
+// contraction, in the workgroups behind the pieces of the base product: it
+// needs X and A only, so it hides behind the stream of W instead of being a
+// launch (and a second one for its own pieces) before it.  They are dispatched
+// last: the tiles seldom fill the last CUs (365 rows, K = N = 4096: 26.8 us with
+// the shrink first, 22.6 last, 22.4 without any, and 10 us for the two launches).  Fragments go from
+// global memory straight into registers, U chunks of 256 columns at a time; the
+// sums are skinny_kernel's to the bit (columns [32w, 32w + 32) of every chunk in
+// one accumulator, w = 0 .. 7, added in order), so the backward's recomputed h
+// and this one agree.  red: LDS for one 16 x 16 tile of 8 partials.
+// ---------------------------------------------------------------------------
+constexpr int kRedBytes = 8 * 16 * 17 * 4;
+
+template <int NW, int NJ>
+__device__ __forceinline__ void shrink_piece(const PartShrink& g, const PartGroup& G, int item, int piece, char* red_) {
+  constexpr int SL = 8 / NW;  // 32-column slices per wave
+  constexpr int U = NJ == 4 ? 2 : 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l15 = lane & 15, g4 = lane >> 4;
+  const int32_t* it = G.items + (int64_t)item * kItemWords;
+  const int a = it[0], begin = it[1], cnt = it[2], r = G.ranks[a];
+  const int nch = (g.C + 255) / 256;
+  const int c0 = piece * g.cpp, c1 = min(nch, c0 + g.cpp);
+  const uint16_t* x[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) x[t] = g.X + (int64_t)G.rows[begin + min(16 * t + l15, cnt - 1)] * g.ldx;
+  const uint16_t* q[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) q[j] = g.A + ((int64_t)a * G.r_max + min(16 * j + l15, r - 1)) * g.C;
+  const bool two = cnt > 16;
+  f32x4 acc[SL][2][NJ];
+#pragma unroll
+  for (int s = 0; s < SL; ++s)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[s][t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < SL; ++s) {
+    const int w = wave + NW * s;
+    for (int c = c0; c < c1; c += U) {
+      u32x4 xv[U][2], qv[U][NJ];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        // chunks past the piece and columns past C read column 0 and count as zeros
+        const int k = (c + u) * 256 + 32 * w + 8 * g4;
+        const int kc = (c + u < c1 && k < g.C) ? k : 0;
+        xv[u][0] = ld16(x[0] + kc);
+        if (two) xv[u][1] = ld16(x[1] + kc);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) qv[u][j] = ld16(q[j] + kc);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (c + u >= c1) break;
+        const bool in = (c + u) * 256 + 32 * w + 8 * g4 < g.C;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) qv[u][j] = in ? qv[u][j] : zero4();
+        xv[u][0] = in ? xv[u][0] : zero4();
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[s][0][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(xv[u][0]), as_bf(qv[u][j]), acc[s][0][j], 0, 0, 0);
+        if (two) {
+          xv[u][1] = in ? xv[u][1] : zero4();
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+            acc[s][1][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(xv[u][1]), as_bf(qv[u][j]), acc[s][1][j], 0, 0, 0);
+        }
+      }
+    }
+  }
+  float* red = reinterpret_cast<float*>(red_);  // [8][16][17]
+  float* part = g.part + (int64_t)piece * G.T * G.r_max;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    if (16 * t >= cnt) break;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      if (16 * j >= r) break;
+#pragma unroll
+      for (int s = 0; s < SL; ++s)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[((wave + NW * s) * 16 + 4 * g4 + v) * 17 + l15] = acc[s][t][j][v];
+      __syncthreads();
+      if (tid < 256) {
+        const int row = tid >> 4, jj = tid & 15;
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) sum += red[(w * 16 + row) * 17 + jj];
+        if (16 * t + row < cnt && 16 * j + jj < r)
+          part[(int64_t)(begin + 16 * t + row) * G.r_max + 16 * j + jj] = sum;
+      }
+      __syncthreads();
+    }
+  }
+}
 
 // ---------------------------------------------------------------------------
 // One workgroup: a TM x TN tile over K-steps [kb, ke) of 64, 4 waves in a
@@ -57,7 +155,8 @@ struct stage_c {
 // Accumulators: weight fragment first, so acc[i][j][v] is output row
 // 16i + lane%16, column 16j + 4(lane/16) + v of the wave's part.
 // ---------------------------------------------------------------------------
-template <bool NN, int TM, int TN, int WGM, int WGN, int NS>
+// NJ: 16-rank tiles of the shrink beside the pieces (0: no shrink in the launch).
+template <bool NN, int NJ, int TM, int TN, int WGM, int WGN, int NS>
 __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(2))) void part_gemm_kernel(PartGroup G) {
   constexpr int TK = 64, NW = WGM * WGN;
   constexpr int WM = TM / WGM, WN = TN / WGN, FM = WM / 16, FN = WN / 16;
@@ -76,6 +175,19 @@ __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(
     else if constexpr (b == 2) return st2;
     else return st3;
   };
+  int bx = blockIdx.x;
+  if constexpr (NJ > 0) {
+    static_assert(STAGE >= kRedBytes, "the shrink's sums fit one buffer");
+    const int sx = bx - G.off[G.n];
+    if (sx >= 0) {
+      int p = 0;
+#pragma unroll
+      for (int i = 1; i < kMaxGroup; ++i) p += (i < G.n && sx >= G.sh_off[i]) ? 1 : 0;
+      const int local = sx - G.sh_off[p];
+      shrink_piece<NW, NJ>(G.sh[p], G, local % G.n_items, local / G.n_items, st0);
+      return;
+    }
+  }
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
   const int l15 = lane & 15, g4 = lane >> 4;
@@ -84,10 +196,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(
   // one weight tile are neighbours on one XCD, then the columns, then the pieces
   int pj = 0;
 #pragma unroll
-  for (int p = 1; p < kMaxGroup; ++p) pj += (p < G.n && (int)blockIdx.x >= G.off[p]) ? 1 : 0;
+  for (int p = 1; p < kMaxGroup; ++p) pj += (p < G.n && bx >= G.off[p]) ? 1 : 0;
   const PartArgs g = G.a[pj];
   const int nwg = G.off[pj + 1] - G.off[pj];
-  const int bid = (int)blockIdx.x - G.off[pj];
+  const int bid = bx - G.off[pj];
   const int per = nwg >> 3, rem = nwg & 7, xcd = bid & 7;
   const int lin = xcd * per + min(xcd, rem) + (bid >> 3);
   const int mt = lin % g.n_m, rest = lin / g.n_m;
@@ -255,8 +367,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(
 // Few rows per item make this a stream of B (and of the pieces): the next
 // block's operands load while the current one is finished.
 // ---------------------------------------------------------------------------
-// NR: 32-rank steps (every rank <= 32 NR); Q16: Q rows of 16-byte aligned rank octets.
-template <bool BWD, int NR, bool Q16>
+// NR: 32-rank steps (every rank <= 32 NR); Q16: Q rows of 16-byte aligned rank
+// octets; HP: h comes as pieces; PF: more than one block per workgroup.
+template <bool BWD, int NR, bool Q16, bool HP, bool PF>
 __global__ __launch_bounds__(256) void part_finish_kernel(FinishGroup G) {
   int pj = 0;
 #pragma unroll
@@ -291,13 +404,13 @@ __global__ __launch_bounds__(256) void part_finish_kernel(FinishGroup G) {
 #pragma unroll
     for (int d = 0; d < 4; ++d)
       mk[s][d] = (2 * d < nv[s] ? 0x0000ffffu : 0u) | (2 * d + 1 < nv[s] ? 0xffff0000u : 0u);
-    lv[s] = ld16(g.L + (int64_t)pr * g.ldl + jc[s]) & mk[s];  // rows padded to 8 entries
+    if constexpr (!HP) lv[s] = ld16(g.L + (int64_t)pr * g.ldl + jc[s]) & mk[s];  // rows padded to 8 entries
   }
   struct Set {
     u32x4 q[NR][4];
     f32x4 p0[4];
   };
-  auto load = [&](int nb, Set& S) {
+  auto load_q = [&](int nb, Set& S) {
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) {
       const int n = min(nb + 16 * ct + l15, g.Nout - 1);
@@ -312,6 +425,8 @@ __global__ __launch_bounds__(256) void part_finish_kernel(FinishGroup G) {
         }
       }
     }
+  };
+  auto load_p = [&](int nb, Set& S) {
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
       S.p0[ct] = *reinterpret_cast<const f32x4*>(src + min(nb + 16 * ct + 4 * g4, g.Nout - 4));
@@ -324,17 +439,18 @@ __global__ __launch_bounds__(256) void part_finish_kernel(FinishGroup G) {
       acc[ct] = S.p0[ct];
       col[ct] = nb + 16 * ct + 4 * g4;
     }
-    // the other pieces in order, four in flight
-    for (int p = 1; p < g.split; p += 4) {
-      f32x4 v[4][4];
+    // the other pieces in order, PB in flight
+    constexpr int PB = 4;
+    for (int p = 1; p < g.split; p += PB) {
+      f32x4 v[PB][4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < PB; ++u)
 #pragma unroll
         for (int ct = 0; ct < 4; ++ct)
           v[u][ct] = *reinterpret_cast<const f32x4*>(src + min(p + u, g.split - 1) * ps + min(col[ct], g.Nout - 4));
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < PB; ++u)
 #pragma unroll
         for (int ct = 0; ct < 4; ++ct) acc[ct] += p + u < g.split ? v[u][ct] : f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -357,8 +473,66 @@ __global__ __launch_bounds__(256) void part_finish_kernel(FinishGroup G) {
             make_uint2(f2bf2(acc[ct][0], acc[ct][1]), f2bf2(acc[ct][2], acc[ct][3]));
     }
   };
+  auto load = [&](int nb, Set& S) {
+    load_q(nb, S);
+    load_p(nb, S);
+  };
   Set s0, s1;
-  load(nb0, s0);
+  load_q(nb0, s0);
+  if constexpr (HP) {
+    // the pieces of the lane's ranks, in piece order, rounded once
+    const float* hp = g.h_part + (int64_t)e * G.r_max;
+    const int64_t hs = (int64_t)g.M * G.r_max;
+    float h[NR][8];
+#pragma unroll
+    for (int s = 0; s < NR; ++s)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) h[s][u] = 0.f;
+    for (int q = 0; q < g.h_pieces; q += 4) {
+      f32x4 v[4][NR][2];
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int s = 0; s < NR; ++s) {
+          const float* p = hp + min(q + w, g.h_pieces - 1) * hs;
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            if constexpr (Q16) {  // entries past the rank are read and masked below
+              v[w][s][u] = *reinterpret_cast<const f32x4*>(p + jc[s] + 4 * u);
+            } else {
+#pragma unroll
+              for (int x = 0; x < 4; ++x) v[w][s][u][x] = p[min(jc[s] + 4 * u + x, r - 1)];
+            }
+          }
+        }
+      __builtin_amdgcn_sched_barrier(0);
+      if (q == 0) load_p(nb0, s0);
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int s = 0; s < NR; ++s)
+#pragma unroll
+          for (int u = 0; u < 8; ++u) h[s][u] += q + w < g.h_pieces ? v[w][s][u >> 2][u & 3] : 0.f;
+    }
+#pragma unroll
+    for (int s = 0; s < NR; ++s) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d) lv[s][d] = f2bf2(h[s][2 * d], h[s][2 * d + 1]) & mk[s][d];
+      if (blockIdx.x == (unsigned)G.yoff[pj] && wave == 0 && g.h_save != nullptr && l15 < cnt) {
+        const int tr = G.row_train[pr];
+        if (tr >= 0)
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (u < nv[s]) g.h_save[(int64_t)tr * G.r_max + jc[s] + u] = (uint16_t)(lv[s][u >> 1] >> (16 * (u & 1)));
+      }
+    }
+  } else {
+    load_p(nb0, s0);
+  }
+  if constexpr (!PF) {
+    finish(nb0, s0);
+    return;
+  }
   for (int nb = nb0; nb < nb_end; nb += 512) {
     if (nb + 256 < nb_end) load(nb + 256, s1);
     finish(nb, s0);
@@ -368,18 +542,18 @@ __global__ __launch_bounds__(256) void part_finish_kernel(FinishGroup G) {
   }
 }
 
-template <bool NN>
+template <bool NN, int NJ>
 hipError_t launch_part(const PartGroup& g, int cfg, hipStream_t s, hipEvent_t start) {
-  const dim3 grid((unsigned)g.off[g.n]), block((unsigned)kPartCfg[cfg].threads);
+  const dim3 grid((unsigned)(g.sh_off[g.n] + g.off[g.n])), block((unsigned)kPartCfg[cfg].threads);
   auto go = [&](auto kernel) {
     if (start) hipExtLaunchKernelGGL(kernel, grid, block, 0, s, start, nullptr, 0, g);
     else hipLaunchKernelGGL(kernel, grid, block, 0, s, g);
   };
   switch (cfg) {
-    case 0: go(part_gemm_kernel<NN, 32, 64, 1, 4, 4>); break;
-    case 1: go(part_gemm_kernel<NN, 64, 128, 2, 4, 4>); break;
-    case 2: go(part_gemm_kernel<NN, 128, 128, 2, 4, 4>); break;
-    case 3: go(part_gemm_kernel<NN, 128, 256, 2, 4, 3>); break;
+    case 0: go(part_gemm_kernel<NN, NJ, 32, 64, 1, 4, 4>); break;
+    case 1: go(part_gemm_kernel<NN, NJ, 64, 128, 2, 4, 4>); break;
+    case 2: go(part_gemm_kernel<NN, NJ, 128, 128, 2, 4, 4>); break;
+    case 3: go(part_gemm_kernel<NN, NJ, 128, 256, 2, 4, 3>); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -387,18 +561,30 @@ hipError_t launch_part(const PartGroup& g, int cfg, hipStream_t s, hipEvent_t st
 
 }  // namespace
 
-hipError_t launch_part_gemm(const PartGroup& g, int cfg, bool nn, hipStream_t s) {
+hipError_t launch_part_gemm(const PartGroup& g, int cfg, int32_t r_sel, bool nn, hipStream_t s) {
   if (g.n <= 0 || g.n > kMaxGroup || g.off[0] != 0 || cfg < 0 || cfg >= kPartCfgs) return hipErrorInvalidValue;
   const PartCfg& pc = kPartCfg[cfg];
+  const bool shrink = g.sh_off[g.n] > 0;
   for (int p = 0; p < g.n; ++p) {
     const PartArgs& a = g.a[p];
     const int64_t nk = (a.C + 63) / 64;
     if (a.M < 1 || a.Nout < 8 || a.C < 8 || a.split < 1 || a.split > nk || !a.part) return hipErrorInvalidValue;
     if (a.n_m != (a.M + pc.tm - 1) / pc.tm || a.n_n != (a.Nout + pc.tn - 1) / pc.tn) return hipErrorInvalidValue;
     if ((int64_t)a.n_m * a.n_n * a.split != g.off[p + 1] - g.off[p]) return hipErrorInvalidValue;
+    if (!shrink) continue;
+    const PartShrink& h = g.sh[p];
+    if (h.C != a.C || h.pieces < 1 || h.cpp < 1 || !h.part || g.sh_off[0] != 0 ||
+        (int64_t)g.n_items * h.pieces != g.sh_off[p + 1] - g.sh_off[p])
+      return hipErrorInvalidValue;
   }
+  if (shrink && (nn || r_sel < 1 || r_sel > 64 || g.T != g.a[0].M)) return hipErrorInvalidValue;
+  if ((int64_t)g.sh_off[g.n] + g.off[g.n] > INT32_MAX) return hipErrorInvalidValue;
   hipEvent_t start = take_launch_start();
-  return nn ? launch_part<true>(g, cfg, s, start) : launch_part<false>(g, cfg, s, start);
+  if (nn) return launch_part<true, 0>(g, cfg, s, start);
+  if (!shrink) return launch_part<false, 0>(g, cfg, s, start);
+  if (r_sel <= 16) return launch_part<false, 1>(g, cfg, s, start);
+  if (r_sel <= 32) return launch_part<false, 2>(g, cfg, s, start);
+  return launch_part<false, 4>(g, cfg, s, start);
 }
 
 hipError_t launch_part_finish(FinishGroup g, int32_t n_items, int32_t r_sel, bool bwd, hipStream_t s) {
@@ -407,8 +593,11 @@ hipError_t launch_part_finish(FinishGroup g, int32_t n_items, int32_t r_sel, boo
   int64_t blocks = 0;
   for (int p = 0; p < g.n; ++p) blocks += (g.a[p].Nout + 255) / 256;
   // Several blocks per workgroup once single ones would give every CU four
-  // workgroups or more: the next block's loads then cover the current one's wait.
-  const int32_t iters = bwd ? 1 : (int32_t)std::max<int64_t>(1, std::min<int64_t>(8, n_items * blocks / 1024));
+  // workgroups or more: the next block's operands then load during the current
+  // one (B of 64 adapters at N = 2 x 14336, 147 MB: 49 us with one block per
+  // workgroup, 40 with four).  With fewer workgroups one block each is faster, in
+  // the form without a second register set (365 rows, N = 4096: 12 against 14 us).
+  const int32_t iters = bwd ? 1 : (int32_t)std::max<int64_t>(1, std::min<int64_t>(4, n_items * blocks / 1024));
   g.yoff[0] = 0;
   for (int p = 0; p < g.n; ++p) {
     g.a[p].iters = iters;
@@ -420,16 +609,26 @@ hipError_t launch_part_finish(FinishGroup g, int32_t n_items, int32_t r_sel, boo
     if (e1) hipExtLaunchKernelGGL(kernel, grid, dim3(256), 0, s, nullptr, e1, 0, g);
     else hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, g);
   };
-  if (bwd) {
-    if (r_sel <= 32) go(part_finish_kernel<true, 1, false>);
-    else go(part_finish_kernel<true, 2, false>);
-  } else if ((g.r_max & 7) == 0) {
-    if (r_sel <= 32) go(part_finish_kernel<false, 1, true>);
-    else go(part_finish_kernel<false, 2, true>);
-  } else {
-    if (r_sel <= 32) go(part_finish_kernel<false, 1, false>);
-    else go(part_finish_kernel<false, 2, false>);
-  }
+  const bool hp = !bwd && g.a[0].h_part != nullptr, q16 = (g.r_max & 7) == 0, wide = r_sel > 32;
+  for (int p = 1; p < g.n; ++p)
+    if ((g.a[p].h_part != nullptr) != hp) return hipErrorInvalidValue;
+  const bool pf = iters > 1;
+  auto fwd = [&](auto nr, auto q, auto h) {
+    constexpr int NR = decltype(nr)::value;
+    constexpr bool Q16 = decltype(q)::value != 0, HP = decltype(h)::value != 0;
+    if (pf) go(part_finish_kernel<false, NR, Q16, HP, true>);
+    else go(part_finish_kernel<false, NR, Q16, HP, false>);
+  };
+  auto fwd_h = [&](auto nr, auto q) {
+    if (hp) fwd(nr, q, stage_c<1>{});
+    else fwd(nr, q, stage_c<0>{});
+  };
+  if (bwd && wide) go(part_finish_kernel<true, 2, false, false, false>);
+  else if (bwd) go(part_finish_kernel<true, 1, false, false, false>);
+  else if (wide && q16) fwd_h(stage_c<2>{}, stage_c<1>{});
+  else if (wide) fwd_h(stage_c<2>{}, stage_c<0>{});
+  else if (q16) fwd_h(stage_c<1>{}, stage_c<1>{});
+  else fwd_h(stage_c<1>{}, stage_c<0>{});
   return hipGetLastError();
 }
 

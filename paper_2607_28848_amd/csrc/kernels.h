@@ -205,10 +205,27 @@ struct PartCfg {
 constexpr int kPartCfgs = 4;
 constexpr PartCfg kPartCfg[kPartCfgs] = {
     {32, 64, 256, 3, 0.25}, {64, 128, 512, 1, 0.33}, {128, 128, 512, 1, 0.5}, {128, 256, 512, 1, 0.85}};
+// The forward's shrink beside the pieces (both read X, neither needs the
+// other): piece q of projection p sums chunks [q cpp, (q + 1) cpp) of 256 columns
+// of h = x A_a^T and writes part[q][T][r_max] in item-list order.
+struct PartShrink {
+  const uint16_t* X;
+  int64_t ldx;
+  const uint16_t* A;     // [n_ad][r_max][C]
+  int32_t C, pieces, cpp;
+  float* part;
+};
 struct PartGroup {
   PartArgs a[kMaxGroup];
   int32_t off[kMaxGroup + 1];  // workgroups [off[p], off[p + 1]) run projection p
   int32_t n;
+  // shrink: the workgroups behind them, [sh_off[p], sh_off[p + 1]) for projection p (all zero: none)
+  PartShrink sh[kMaxGroup];
+  int32_t sh_off[kMaxGroup + 1];
+  const int32_t* items;  // {adapter, begin, count <= 32, aux}
+  const int32_t* rows;   // item element -> token row
+  const int32_t* ranks;
+  int32_t n_items, T, r_max;
 };
 // The sum of a projection's pieces plus the low-rank term of every row.
 struct FinishArgs {
@@ -216,6 +233,12 @@ struct FinishArgs {
   int32_t split, M, Nout;
   const uint16_t* L;     // h of every token row (forward), g of the compact training rows (backward)
   int64_t ldl;
+  // forward with the shrink beside the pieces: h as pieces [h_pieces][M][r_max] in
+  // item-list order, summed in order and rounded once here (L unused); training
+  // rows also go to H_save (nullptr: not kept)
+  const float* h_part;
+  int32_t h_pieces;
+  uint16_t* h_save;
   const uint16_t* Q;     // B [n_ad][Nout][r_max] (forward), A [n_ad][r_max][Nout] (backward)
   uint16_t* out;
   int64_t ldo;
@@ -230,6 +253,7 @@ struct FinishGroup {
   int32_t n, r_max;
   const int32_t* items;  // {adapter, begin, count, aux}: <= 32 rows (forward), <= 16 (backward)
   const int32_t* rows;   // forward: item element -> token row; backward: nullptr (compact rows)
+  const int32_t* row_train;  // forward: compact training row of a token row, or -1
   const int32_t* ranks;
   const float* scales;   // nullptr: scale 1
 };
@@ -257,7 +281,7 @@ hipError_t launch_gemm_nn(const GemmArgs& a, int tm, int tn, hipStream_t s);
 hipEvent_t take_launch_start();
 hipEvent_t take_launch_stop();
 // The pieces' kernel in configuration cfg (kPartCfg), and the sum of the pieces.
-hipError_t launch_part_gemm(const PartGroup& g, int cfg, bool nn, hipStream_t s);
+hipError_t launch_part_gemm(const PartGroup& g, int cfg, int32_t r_sel, bool nn, hipStream_t s);
 hipError_t launch_part_finish(FinishGroup g, int32_t n_items, int32_t r_sel, bool bwd, hipStream_t s);
 // Rank-r contractions: r_sel bounds the rank of every item's adapter (it sizes
 // the rank tiles); the partials of a split contraction have stride a.r_max.
