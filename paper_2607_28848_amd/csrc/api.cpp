@@ -689,6 +689,10 @@ int fwd_impl(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N, const void* 
     a.drop_scale = ds.scale;
     a.row_adapter = p->dptr(L.row_adapter);
     a.row_train = p->dptr(L.row_train);
+    a.shrink_items = p->dptr(L.shrink_items);
+    a.shrink_rows = p->dptr(L.shrink_rows);
+    a.n_shrink = p->n_shrink;
+    a.r_used = p->r_used;
     a.ranks = ranks;
     a.scales = scales;
     a.X = static_cast<const float*>(X);
@@ -884,6 +888,9 @@ int bwd_impl(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N, const void* 
     a.tad_ptr = p->dptr(L.tad_chunk_ptr);
     a.tad_chunks = p->dptr(L.tad_chunks);
     a.chunks = p->dptr(L.chunks);
+    a.train_items = p->dptr(L.train_items);
+    a.n_titems = p->n_titems;
+    a.r_train = p->r_train;
     a.ranks = ranks;
     a.scales = scales;
     a.X = static_cast<const float*>(X);

@@ -378,7 +378,7 @@ hipError_t launch_dropout_mask_group(const DropoutMaskGroup& g, int32_t Tt, hipS
 hipError_t launch_dropout_mask(uint32_t* bits, int32_t Tt, int32_t K, const DropoutSpec& d, hipStream_t s);
 
 
-// Launchers (fp32 mode: plain FMA kernels, same semantics).
+// Launchers (fp32 mode, same semantics).
 struct F32Args {
   int32_t T, Tt, K, N, r_max;
   const int32_t* row_adapter;
@@ -392,6 +392,9 @@ struct F32Args {
   const int32_t* chunks;
   const int32_t* ranks;
   const float* scales;
+  const int32_t *shrink_items, *shrink_rows, *train_items;  // work items: rows of one adapter (<= 32, <= 16)
+  int32_t n_shrink, n_titems;
+  int32_t r_used, r_train;  // largest rank of an adapter with rows / with training rows
   const float *X, *W, *A, *B, *Hs, *dY;
   float *Y, *Hsave, *Hall, *G, *dA, *dB, *dX;
   int64_t ldx, ldw, ldy, lddy, lddx;  // row strides of X, W, Y, dY, dX
