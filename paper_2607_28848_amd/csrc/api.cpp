@@ -42,16 +42,23 @@ int device_cus() {
 //     kMinSkIters K-steps each), so that wave takes 1/s of a tile's time,
 //     plus kSplitCost64 for the pieces' fp32 partials and the kernel that sums
 //     them (relative to a tile of 64 K-steps, so smaller for longer tiles).
+//   the same with the r <= CUs / 2 tiles of a last, partial wave run as two
+//     halves of 128 rows each, on twice the CUs (no pieces to sum, and the same
+//     bits as whole tiles; 6144 x 4096 x 4096, 1.5 waves: 160 us, against 182 with
+//     the tiles split in two).  Among the 256 x 256 forms only: the masked
+//     low-rank term of the 128 x 128 form keeps a NaN in its own column, that of
+//     the 256 x 256 form does not.
 // The constants were fitted to timings of the Llama-3-8B projections
 // (forward and dX) on MI355X.
 struct GemmPlan {
   int tm = 128, tn = 128;
   int32_t n_mtiles = 0, n_ntiles = 0;
-  int32_t dp_tiles = 0, sk_tiles = 0, sk_split = 0;
+  int32_t dp_tiles = 0, sk_tiles = 0, sk_split = 0, half_tiles = 0;
 };
 constexpr int kMinSkIters = 8;
 constexpr double kEff256 = 1.12;
 constexpr double kSplitCost64 = 0.4;
+constexpr double kHalfTile = 0.55;
 
 GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool allow_split = true) {
   GemmPlan best;
@@ -84,7 +91,13 @@ GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool al
       p.sk_split = (int32_t)split;
     }
   }
-  return cost256 < cost128 ? p : best;
+  if (cost256 >= cost128) return best;
+  if (r > 0 && 2 * r <= cus && ((double)full + kHalfTile) * 4.0 / kEff256 < cost256) {
+    p.dp_tiles = (int32_t)(full * cus);
+    p.half_tiles = (int32_t)r;
+    p.sk_tiles = p.sk_split = 0;
+  }
+  return p;
 }
 
 // GEMM in pieces (launch_part_gemm) for a batch's projections, or the tile
@@ -93,13 +106,16 @@ GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool al
 //            configuration's time per step (at least the weights at 5.5 TB/s),
 //            plus the fp32 pieces written and read once each at 5 TB/s and the
 //            launch that sums them
-//   tiles    the 128 x 128 form's rounds at 1.0 us per K-step or the 256 x 256
-//            form's at 1.5 us (a split last round and its sum: 1/split of a round
-//            and the pieces' bytes); gathered rows cost another launch
+//   tiles    the 128 x 128 form's rounds at 1.0 us per K-step (0.45 with one
+//            workgroup per CU) or the 256 x 256 form's at 1.4 us (half tiles: 0.7 of
+//            it; a split last round and its sum: 1/split of it and the pieces'
+//            bytes); gathered rows cost another launch
 // Fitted to timings of M = 8 .. 2048 rows of the Llama-3-8B shapes on MI355X:
 // the pieces win below about 500 rows (M = 96, N = K = 4096: 19.0 against 32.5
 // us; M = 256, K = 14336: 50.9 against 59.3), the tiles above (M = 1500, K = N =
-// 4096: 57.9 against 71.0).
+// 4096: 57.9 against 71.0), where only a clear gain takes the pieces.  Up to
+// kPartRows rows the pieces are taken whatever the estimate: they won or tied at
+// every shape timed, and so a group's projections all run in pieces or none does.
 struct PartPlan {
   bool use = false;
   int cfg = 0;
@@ -107,16 +123,16 @@ struct PartPlan {
   size_t off[kMaxGroup] = {}, bytes = 0;  // the pieces' buffers, past the rest of the workspace
   size_t h_off[kMaxGroup] = {};           // forward: the shrink's pieces
 };
-constexpr int kMinPartSteps = 4;
-constexpr double kPartBytesPerUs = 5e6, kWeightBytesPerUs = 5.5e6, kSumUs = 4.0, kGatherUs = 6.0;
+constexpr int kMinPartSteps = 4, kPartRows = 256;
+constexpr double kPartBytesPerUs = 5e6, kWeightBytesPerUs = 5.5e6, kSumUs = 4.0, kGatherUs = 6.0, kTileStepUs = 1.4;
 
 double tiles_us(const GemmPlan& g, int32_t C) {
   const int64_t cus = device_cus(), nk = (C + 63) / 64;
   if (cus <= 0) return 0.0;  // no device: no launch plan either
-  if (g.tm == 128) return (double)((g.dp_tiles + 2 * cus - 1) / (2 * cus)) * nk * 1.0;
-  double t = (double)((g.dp_tiles + cus - 1) / cus) * nk * 1.5;
+  if (g.tm == 128) return g.dp_tiles <= cus ? nk * 0.45 : (double)((g.dp_tiles + 2 * cus - 1) / (2 * cus)) * nk;
+  double t = ((double)((g.dp_tiles + cus - 1) / cus) + (g.half_tiles > 0 ? 0.7 : 0.0)) * nk * kTileStepUs;
   if (g.sk_tiles > 0)
-    t += 1.5 * nk / g.sk_split + kSumUs + (double)g.sk_tiles * g.sk_split * g.tm * g.tn * 8 / kPartBytesPerUs;
+    t += kTileStepUs * nk / g.sk_split + kSumUs + (double)g.sk_tiles * g.sk_split * g.tm * g.tn * 8 / kPartBytesPerUs;
   return t;
 }
 
@@ -126,7 +142,7 @@ PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout,
   const int cus = device_cus();
   if (cus <= 0 || M <= 0) return best;
   static const int kSplits[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
-  double w_us = 0, t_best = t_tiles - kSumUs;
+  double w_us = 0, t_best = M <= kPartRows ? HUGE_VAL : (M > 512 ? 0.85 * t_tiles : t_tiles) - kSumUs;
   int32_t nk[kMaxGroup], nk_max = 1;
   for (int i = 0; i < n; ++i) {
     nk[i] = (C[i] + 63) / 64;
@@ -278,7 +294,8 @@ PartPlan group_part_plan(const dsv_plan& p, int pass, int32_t n, const Proj* pr,
     longest = std::max(longest, nk);
   }
   // tiles in rounds over the CUs, the longest contraction setting the round
-  const double whole = std::ceil(steps / cus / longest) * longest * 1.5 + (pass == 0 && p.n_gather > 0 ? kGatherUs : 0.0);
+  const double rounds = steps / cus / longest, part = rounds - std::floor(rounds);
+  const double whole = (std::floor(rounds) + (part > 0.5 ? 1.0 : part > 0.0 ? 0.7 : 0.0)) * longest * kTileStepUs + (pass == 0 && p.n_gather > 0 ? kGatherUs : 0.0);
   const PartPlan pp = part_plan(pass == 0 ? &p : nullptr, M, n, Nout, C, whole);
   for (int i = 0; pp.use && i < n; ++i)
     if (!(pass == 0 ? fwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N) : bwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N)).sk_tiles &&
@@ -350,6 +367,7 @@ void set_split(GemmArgs& g, const GemmPlan& gp, void* ws, size_t part_off) {
   g.dp_tiles = gp.dp_tiles;
   g.sk_tiles = gp.sk_tiles;
   g.sk_split = gp.sk_split;
+  g.half_tiles = gp.half_tiles;
   g.sk_part = gp.sk_tiles > 0 ? at<float>(ws, part_off) : nullptr;
 }
 
@@ -1051,6 +1069,10 @@ int bwd_impl(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N, const void* 
     g.tiles = p->dptr(gp.tm == 256 ? L.bwd_tiles : L.bwd_tiles128);
     g.uniform_rows = gp.tm == 256 && p->btiles_uniform;
     set_split(g, gp, workspace, ws.sk_part);
+    if (g.half_tiles > 0 && !Wt && !nn16_fits(g)) {  // the 8-wave form has whole tiles only
+      g.dp_tiles += g.half_tiles;
+      g.half_tiles = 0;
+    }
     g.Lp = gm;
     g.ldl = ldh;
     g.Lq = static_cast<const uint16_t*>(A);
@@ -1137,6 +1159,26 @@ GemmPlan whole256(int32_t m256, int32_t n_out) {
   g.n_ntiles = (n_out + 255) / 256;
   g.dp_tiles = g.n_mtiles * g.n_ntiles;
   return g;
+}
+
+// Halves the tiles of a grouped launch's last, partial wave where they fill at
+// most half the CUs (plan_gemm's rule).  Only for projections of one contraction
+// length, whose waves end together; ok: the launch's kernels have half tiles.
+void halve_last_wave(GemmGroup& G, bool ok) {
+  const int cus = device_cus();
+  for (int p = 1; p < G.n; ++p) ok = ok && (G.a[p].C + 63) / 64 == (G.a[0].C + 63) / 64;
+  int32_t r = ok && cus > 0 ? G.off[G.n] % cus : 0;
+  if (2 * r > cus) r = 0;
+  for (int p = G.n - 1; p >= 0 && r > 0; --p) {
+    GemmArgs& g = G.a[p];
+    g.half_tiles = std::min(r, g.dp_tiles);
+    g.dp_tiles -= g.half_tiles;
+    r -= g.half_tiles;
+  }
+  for (int p = 0; p < G.n; ++p) {
+    G.off[p + 1] = G.off[p] + G.a[p].dp_tiles;
+    G.hoff[p + 1] = G.hoff[p] + 2 * G.a[p].half_tiles;
+  }
 }
 
 int check_group(const dsv_plan* p, dsv_dtype dt, int32_t n, const void* projs) {
@@ -1396,6 +1438,7 @@ int fwd_grouped_impl(const dsv_plan* p, dsv_dtype dt, int32_t n_proj, const dsv_
     g.gslot = p->dptr(L.gslot);
     G.off[k + 1] = G.off[k] + g.n_mtiles * g.n_ntiles;
   }
+  halve_last_wave(G, true);
   const int tk = timing_begin(0, s);
   const hipError_t e = launch_gemm_group_nt(G, s);
   timing_end(tk, s);
@@ -1646,6 +1689,9 @@ int bwd_grouped_impl(const dsv_plan* p, dsv_dtype dt, int32_t n_proj, const dsv_
         ++G.n;
       }
       if (G.n > 0) {
+        bool ok = true;
+        for (int k = 0; k < G.n; ++k) ok = ok && (nt || nn16_fits(G.a[k]));
+        halve_last_wave(G, ok);
         const int tk = timing_begin(1, s);
         const hipError_t e = nt ? launch_gemm_group_nt(G, s) : launch_gemm_group_nn(G, s);
         timing_end(tk, s);

@@ -581,15 +581,19 @@ __device__ __forceinline__ u32x2v ld4_sel(const uint16_t* p, int64_t stride, int
 
 // DROP: the instantiation that masks the low-rank term (dX under LoRA
 // dropout); the others carry no masking code.
-template <bool SK, bool DROP, bool NN>
+// FM: 16-row blocks per wave.  8: the 256 x 256 tile.  4: rows [128 half, 128 half
+// + 128) of it, for a last partial round of tiles, which as half tiles fills
+// twice the CUs (the same sums per element, so the same bits).
+template <bool SK, bool DROP, bool NN, int FM>
 __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, char* smem1, int tid, int lin, int t_sk,
                                              int piece,
-                                             int kb, int ke, int nk) {
-  constexpr int TM = 256, TN = 256, TK = 64, NW = 4, WM = 128, WN = 128, FM = 8, FN = 8;
+                                             int kb, int ke, int nk, int half = 0) {
+  constexpr int WM = 16 * FM, TM = 2 * WM, TN = 256, TK = 64, NW = 4, WN = 128, FN = 8;
   constexpr int ROWB = TK * 2;                   // bytes per LDS row
   constexpr int A_BYTES = TM * ROWB, STAGE = A_BYTES + TN * ROWB;
-  constexpr int LOADS = TM * ROWB / 1024 / 4;    // 1 KiB direct loads per wave per operand
-  static_assert(LOADS == 8 && TN == TM, "load split");
+  constexpr int LOADS = TN * ROWB / 1024 / 4;    // 1 KiB direct loads per wave of the weight tile
+  constexpr int LOADS_A = TM * ROWB / 1024 / 4;  // ... and of the row tile
+  static_assert(LOADS == 8 && LOADS_A == FM, "load split");
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   // The two pipeline buffers are two LDS arrays: with the buffer index a
@@ -602,15 +606,17 @@ __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, cha
   tile_coords(g, lin, mt, nt);
   const int32_t* td = g.tiles + (int64_t)mt * kTileWords;
   // uniform rows: the first loads need not wait for the tile descriptor
-  const int m0 = g.uniform_rows ? mt * TM : td[0];
-  const int nrows = g.uniform_rows ? min(TM, g.M - m0) : td[3];
+  const int r0 = FM == 8 ? 0 : 128 * half;  // first row within the 256-row tile
+  const int m0 = (g.uniform_rows ? mt * 256 : td[0]) + r0;
+  const int nrows = g.uniform_rows ? min(TM, g.M - m0) : min(TM, td[3] - r0);
+  if (FM < 8 && nrows <= 0) return;  // the tile ends in its first half
   const int n0 = nt * TN;
   // Everything the first low-rank group needs is read here, before the first
   // direct load: past those loads a read of kernel-visible memory can no
   // longer be a scalar load, and a vector load would wait for every load
   // issued before it (vector-memory operations complete in order).
   const int ngroups = td[1], has_gather = td[2];
-  const int g0_a = td[4], g0_lo = td[5], g0_hi = td[6];  // zeros when the tile has no group
+  const int g0_a = td[4], g0_lo = td[5] - r0, g0_hi = td[6] - r0;  // zeros when the tile has no group
   const int g0_r = g.ranks[g0_a];
   const float g0_sc = g.scales ? g.scales[g0_a] : 1.f;
   // NT: both operands are contraction-contiguous rows; the lane offsets are
@@ -639,6 +645,10 @@ __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, cha
   int voff[LOADS];
 #pragma unroll
   for (int i = 0; i < LOADS; ++i) voff[i] = ((((lane & 7) ^ lr ^ i) << 4)) + lr * ld * 2;
+  int voff_a[LOADS_A];  // the row tile's: q = LOADS_A wave + i
+#pragma unroll
+  for (int i = 0; i < LOADS_A; ++i)
+    voff_a[i] = FM == 8 ? voff[i] : ((((lane & 7) ^ lr ^ ((LOADS_A * wave + i) & 7)) << 4)) + lr * ld * 2;
   // NN weight loads: load i fills tile rows 2q, 2q+1 (q = 8 wave + i, 512
   // bytes each), lane ln taking row 2q + ln/32, slot ln%32, which holds the
   // row's 16-byte chunk (ln%32) ^ nn_swz(row); nn_swz(row) depends on i%2 only.
@@ -663,9 +673,9 @@ __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, cha
     const int kbytes = kt * TK * 2;
     char* sa = buf(stage);
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-      const int q = wave * LOADS + i;
-      llvm_amdgcn_raw_buffer_load_lds(ra, (lds_u32*)(sa + q * 1024), 16, voff[i],
+    for (int i = 0; i < LOADS_A; ++i) {
+      const int q = wave * LOADS_A + i;
+      llvm_amdgcn_raw_buffer_load_lds(ra, (lds_u32*)(sa + q * 1024), 16, voff_a[i],
                                       __builtin_amdgcn_readfirstlane(q * 16 * ld + kbytes), 0, 0);
     }
 #pragma unroll
@@ -680,17 +690,22 @@ __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, cha
     }
     char* sa = buf(stage);
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-      const int q = wave * LOADS + i;
+    for (int i = 0; i < LOADS_A; ++i) {
+      const int q = wave * LOADS_A + i;
       const int row = 8 * q + lr;
       const int c = (lane & 7) ^ swz<TK>(row);
-      const bool in_c = k0 + 8 * c < g.C;
-      const int vo = in_c ? (row * ld + k0 + 8 * c) * 2 : (int)0x7FFFFFF0;
+      const int vo = k0 + 8 * c < g.C ? (row * ld + k0 + 8 * c) * 2 : (int)0x7FFFFFF0;
       llvm_amdgcn_raw_buffer_load_lds(ra, (lds_u32*)(sa + q * 1024), 16, vo, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
       if constexpr (NN) {
         load_b(kt, sa, i);  // rows past the contraction lie past the descriptor
       } else {
-        const int vb = in_c ? (row * ldq + k0 + 8 * c) * 2 : (int)0x7FFFFFF0;
+        const int q = wave * LOADS + i;
+        const int row = 8 * q + lr;
+        const int c = (lane & 7) ^ swz<TK>(row);
+        const int vb = k0 + 8 * c < g.C ? (row * ldq + k0 + 8 * c) * 2 : (int)0x7FFFFFF0;
         llvm_amdgcn_raw_buffer_load_lds(rb, (lds_u32*)(sa + A_BYTES + q * 1024), 16, vb, 0, 0, 0);
       }
     }
@@ -782,8 +797,8 @@ __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, cha
   if (pre) lr_mfma(pre_h, pre_b, g0_lo, g0_hi, 4, g0_sc);
   // every other (group, 16-rank step) of the tile
   for (int gi = 0; !DROP && kb == 0 && gi < ngroups; ++gi) {
-    const int a = gi == 0 ? g0_a : td[4 + 3 * gi], lo = gi == 0 ? g0_lo : td[5 + 3 * gi];
-    const int hi = gi == 0 ? g0_hi : td[6 + 3 * gi];
+    const int a = gi == 0 ? g0_a : td[4 + 3 * gi], lo = gi == 0 ? g0_lo : td[5 + 3 * gi] - r0;
+    const int hi = gi == 0 ? g0_hi : td[6 + 3 * gi] - r0;
     if (hi <= wm * WM || lo >= wm * WM + WM) continue;  // no row of this wave
     const int r = gi == 0 ? g0_r : g.ranks[a];
     const float sc = gi == 0 ? g0_sc : (g.scales ? g.scales[a] : 1.f);
@@ -901,7 +916,7 @@ __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, cha
         if (g0_hi > rb0 && g0_lo < rb0 + 16) lr_row(t, hv1, b1, row, g0_lo, g0_hi, min(4, g0_r - jb0), g0_sc);
       } else {
         for (int gi = 0; gi < ngroups; ++gi) {
-          const int a = td[4 + 3 * gi], lo = td[5 + 3 * gi], hi = td[6 + 3 * gi];
+          const int a = td[4 + 3 * gi], lo = td[5 + 3 * gi] - r0, hi = td[6 + 3 * gi] - r0;
           if (hi <= rb0 || lo >= rb0 + 16) continue;  // no row of this block
           const int r = g.ranks[a];
           const float sc = g.scales ? g.scales[a] : 1.f;
@@ -980,7 +995,7 @@ __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, cha
   // set whose fragment j is replaced by the next step's once the 8 MFMAs of
   // column block j have been issued.
   bf16x8 fa0[FM], fa1[FM], fb[FN];
-  if (ke - kb >= 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * LOADS));  // first K-step landed
+  if (ke - kb >= 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS_A + LOADS));  // first K-step landed
   else vmem_wait_all();
   __syncthreads();
 #pragma unroll
@@ -988,18 +1003,17 @@ __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, cha
 #pragma unroll
   for (int i = 0; i < FM; ++i) fa0[i] = rd_a(smem0, 0, i);
 
-  // Direct loads of whole K-step kl into buffer ls: load n of the wave's 16
-  // (A for n < 8, B after).  A texture unit takes a 1 KiB load in about 16
+  // Direct loads of whole K-step kl into buffer ls: load n of the wave's
+  // LOADS_A + LOADS (A first).  A texture unit takes a 1 KiB load in about 16
   // cycles, so the 64 loads a K-step needs per CU are spread evenly, two per
   // wave per column block (a block's 8 MFMAs take 128 cycles), over the
   // second step, after the barrier that frees their buffer.
   auto load_n = [&](int kl, int ls, int n) {
-    const int i = n & 7;
-    const int q = wave * LOADS + i;
-    if (n >= 8)
-      load_b(kl, buf(ls), i);
+    const int q = wave * LOADS_A + n;
+    if (n >= LOADS_A)
+      load_b(kl, buf(ls), n - LOADS_A);
     else
-      llvm_amdgcn_raw_buffer_load_lds(ra, (lds_u32*)(buf(ls) + q * 1024), 16, voff[i],
+      llvm_amdgcn_raw_buffer_load_lds(ra, (lds_u32*)(buf(ls) + q * 1024), 16, voff_a[n < LOADS_A ? n : 0],
                                       __builtin_amdgcn_readfirstlane(q * 16 * ld + kl * TK * 2), 0, 0);
   };
   // One 32-wide step with fragments (cur, fb); reads the next step's
@@ -1007,7 +1021,7 @@ __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, cha
   // by scheduling fences, per column block j: its 8 MFMAs, then (when `load`)
   // loads 2j, 2j+1 of whole K-step kl into buffer ls, then the next B
   // fragment j (replacing fb[j] once block j's MFMAs are issued) and A
-  // fragments 2j, 2j+1 (blocks 0-3).
+  // fragments 2j, 2j+1 (the first FM / 2 blocks).
   auto step = [&](bf16x8 (&cur)[FM], bf16x8 (&nxt)[FM], const char* st_next, int s_next, bool load, int kl,
                   int ls) {
 #pragma unroll
@@ -1015,11 +1029,11 @@ __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, cha
 #pragma unroll
       for (int i = 0; i < FM; ++i)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], cur[i], acc[i][j], 0, 0, 0);
-      if (load) {
+      if (load && 2 * j < LOADS_A + LOADS) {
         load_n(kl, ls, 2 * j);
         load_n(kl, ls, 2 * j + 1);
       }
-      if (j < 4) {
+      if (j < FM / 2) {
         nxt[2 * j] = rd_a(st_next, s_next, 2 * j);
         nxt[2 * j + 1] = rd_a(st_next, s_next, 2 * j + 1);
       }
@@ -1067,7 +1081,7 @@ __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, cha
   const int last_stage = stage;
 
   // ---- a piece of a split tile: its fp32 partial goes to its slot --------
-  if (SK && !(kb == 0 && ke == nk)) {
+  if (SK && FM == 8 && !(kb == 0 && ke == nk)) {
     float* part = g.sk_part + (int64_t)(t_sk * g.sk_split + piece) * (TM * TN);
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
@@ -1172,14 +1186,22 @@ __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, cha
     epilogue(bool_c<false>{});
 }
 
-template <bool SK, bool DROP, bool NN>
+// HALF: the last half_tiles tiles run as two half tiles each.
+template <bool SK, bool DROP, bool NN, bool HALF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm16_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(1024))) char smem0[2 * 256 * 64 * 2];
   __shared__ __attribute__((aligned(1024))) char smem1[2 * 256 * 64 * 2];
   const int nk = (g.C + 63) / 64;
+  if constexpr (HALF) {
+    if ((int)blockIdx.x >= g.dp_tiles) {
+      const int q = xcd_major(blockIdx.x - g.dp_tiles, gridDim.x - g.dp_tiles);
+      gemm_piece16<false, DROP, NN, 4>(g, smem0, smem1, threadIdx.x, g.dp_tiles + (q >> 1), -1, 0, 0, nk, nk, q & 1);
+      return;
+    }
+  }
   int lin, t_sk = -1, piece = 0, kb = 0, ke = nk;
   if (!SK || (int)blockIdx.x < g.dp_tiles) {
-    lin = xcd_major(blockIdx.x, SK ? g.dp_tiles : gridDim.x);
+    lin = xcd_major(blockIdx.x, SK || HALF ? g.dp_tiles : gridDim.x);
   } else {
     const int q = xcd_major(blockIdx.x - g.dp_tiles, gridDim.x - g.dp_tiles);
     piece = q / g.sk_tiles;
@@ -1188,23 +1210,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     kb = (int)(((int64_t)piece * nk) / g.sk_split);
     ke = (int)(((int64_t)(piece + 1) * nk) / g.sk_split);
   }
-  gemm_piece16<SK, DROP, NN>(g, smem0, smem1, threadIdx.x, lin, t_sk, piece, kb, ke, nk);
+  gemm_piece16<SK, DROP, NN, 8>(g, smem0, smem1, threadIdx.x, lin, t_sk, piece, kb, ke, nk);
 }
 
-template <bool DROP, bool NN>
+template <bool DROP, bool NN, bool HALF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm16_group_kernel(GemmGroup G) {
   __shared__ __attribute__((aligned(1024))) char smem0[2 * 256 * 64 * 2];
   __shared__ __attribute__((aligned(1024))) char smem1[2 * 256 * 64 * 2];
   // the workgroup's projection: every boundary compared at once (one batch
   // of argument loads instead of one dependent load per projection)
   int pj = 0;
+  if constexpr (HALF) {
+    const int hx = (int)blockIdx.x - G.off[G.n];
+    if (hx >= 0) {
+#pragma unroll
+      for (int p = 1; p < kMaxGroup; ++p) pj += (p < G.n && hx >= G.hoff[p]) ? 1 : 0;
+      const GemmArgs g = G.a[pj];
+      const int q = xcd_major(hx - G.hoff[pj], G.hoff[pj + 1] - G.hoff[pj]);
+      const int nk = (g.C + 63) / 64;
+      gemm_piece16<false, DROP, NN, 4>(g, smem0, smem1, threadIdx.x, g.dp_tiles + (q >> 1), -1, 0, 0, nk, nk, q & 1);
+      return;
+    }
+  }
 #pragma unroll
   for (int p = 1; p < kMaxGroup; ++p) pj += (p < G.n && (int)blockIdx.x >= G.off[p]) ? 1 : 0;
   const GemmArgs g = G.a[pj];
   const int local = (int)blockIdx.x - G.off[pj];
   const int lin = xcd_major(local, G.off[pj + 1] - G.off[pj]);
   const int nk = (g.C + 63) / 64;
-  gemm_piece16<false, DROP, NN>(g, smem0, smem1, threadIdx.x, lin, -1, 0, 0, nk, nk);
+  gemm_piece16<false, DROP, NN, 8>(g, smem0, smem1, threadIdx.x, lin, -1, 0, 0, nk, nk);
 }
 
 // ---------------------------------------------------------------------------
@@ -1261,15 +1295,14 @@ void launch_timed(F kernel, dim3 grid, dim3 block, hipStream_t s, bool first, bo
 // Tile configurations: (TM, TN, wave grid, K-step, pipeline stages); two
 // waves per SIMD in each (8 waves per 256-row workgroup, or two 4-wave
 // 128 x 128 workgroups per CU).
-// The 16x16x32 NN form addresses the weight with 32-bit byte offsets from the
-// tile's first column, one K-step past the contraction at most.
-bool nn16_fits(const GemmArgs& a) { return ((int64_t)a.C + 64) * a.ldq * 2 < ((int64_t)1 << 31); }
-
 template <bool NN>
 hipError_t launch_gemm_tiled(const GemmArgs& a, int tm, int tn, hipStream_t s) {
   if (a.n_mtiles <= 0 || a.n_ntiles <= 0) return hipSuccess;
   const int64_t tiles = (int64_t)a.n_mtiles * a.n_ntiles;
-  if (a.dp_tiles < 0 || a.sk_tiles < 0 || a.dp_tiles + (int64_t)a.sk_tiles != tiles) return hipErrorInvalidValue;
+  if (a.dp_tiles < 0 || a.sk_tiles < 0 || a.half_tiles < 0 || a.dp_tiles + (int64_t)a.sk_tiles + a.half_tiles != tiles)
+    return hipErrorInvalidValue;
+  // half tiles: 256 x 256 tiles of the 16x16x32 form, none split as well
+  if (a.half_tiles > 0 && (tm != 256 || tn != 256 || a.sk_tiles > 0 || (NN && !nn16_fits(a)))) return hipErrorInvalidValue;
   if (a.sk_tiles > 0) {
     // split tiles: 256x256 only, whole tiles a multiple of 8 (the pieces keep
     // the hardware's XCD round robin), and at least one K-step per piece
@@ -1277,23 +1310,26 @@ hipError_t launch_gemm_tiled(const GemmArgs& a, int tm, int tn, hipStream_t s) {
     if (tm != 256 || tn != 256 || (a.dp_tiles & 7) || a.sk_split < 2 || a.sk_split > nk || !a.sk_part)
       return hipErrorInvalidValue;
   }
-  const dim3 grid((unsigned)(a.dp_tiles + (int64_t)a.sk_tiles * (a.sk_tiles > 0 ? a.sk_split : 0)));
+  const dim3 grid((unsigned)(a.dp_tiles + (int64_t)a.sk_tiles * (a.sk_tiles > 0 ? a.sk_split : 0) + 2 * (int64_t)a.half_tiles));
   if constexpr (!NN) {
     // 256 x 256 NT tiles: the 16x16x32 form (both operands rows of the
     // contraction, each with its own row stride)
     if (tm == 256 && tn == 256) {
       const bool drop = a.keep != nullptr;
       if (a.sk_tiles > 0) {
-        if (drop) launch_timed(gemm16_kernel<true, true, false>, grid, dim3(256), s, true, false, a);
-        else launch_timed(gemm16_kernel<true, false, false>, grid, dim3(256), s, true, false, a);
+        if (drop) launch_timed(gemm16_kernel<true, true, false, false>, grid, dim3(256), s, true, false, a);
+        else launch_timed(gemm16_kernel<true, false, false, false>, grid, dim3(256), s, true, false, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         launch_timed(split_fixup_kernel<NN, 256, 256>, dim3((unsigned)a.sk_tiles * (256 * 256 / 4 / 256)), dim3(256),
                      s, false, true, a);
+      } else if (a.half_tiles > 0) {
+        if (drop) launch_timed(gemm16_kernel<false, true, false, true>, grid, dim3(256), s, true, true, a);
+        else launch_timed(gemm16_kernel<false, false, false, true>, grid, dim3(256), s, true, true, a);
       } else if (drop) {
-        launch_timed(gemm16_kernel<false, true, false>, grid, dim3(256), s, true, true, a);
+        launch_timed(gemm16_kernel<false, true, false, false>, grid, dim3(256), s, true, true, a);
       } else {
-        launch_timed(gemm16_kernel<false, false, false>, grid, dim3(256), s, true, true, a);
+        launch_timed(gemm16_kernel<false, false, false, false>, grid, dim3(256), s, true, true, a);
       }
       return hipGetLastError();
     }
@@ -1302,16 +1338,19 @@ hipError_t launch_gemm_tiled(const GemmArgs& a, int tm, int tn, hipStream_t s) {
     if (tm == 256 && tn == 256 && nn16_fits(a)) {
       const bool drop = a.keep != nullptr;
       if (a.sk_tiles > 0) {
-        if (drop) launch_timed(gemm16_kernel<true, true, true>, grid, dim3(256), s, true, false, a);
-        else launch_timed(gemm16_kernel<true, false, true>, grid, dim3(256), s, true, false, a);
+        if (drop) launch_timed(gemm16_kernel<true, true, true, false>, grid, dim3(256), s, true, false, a);
+        else launch_timed(gemm16_kernel<true, false, true, false>, grid, dim3(256), s, true, false, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         launch_timed(split_fixup_kernel<NN, 256, 256>, dim3((unsigned)a.sk_tiles * (256 * 256 / 4 / 256)), dim3(256),
                      s, false, true, a);
+      } else if (a.half_tiles > 0) {
+        if (drop) launch_timed(gemm16_kernel<false, true, true, true>, grid, dim3(256), s, true, true, a);
+        else launch_timed(gemm16_kernel<false, false, true, true>, grid, dim3(256), s, true, true, a);
       } else if (drop) {
-        launch_timed(gemm16_kernel<false, true, true>, grid, dim3(256), s, true, true, a);
+        launch_timed(gemm16_kernel<false, true, true, false>, grid, dim3(256), s, true, true, a);
       } else {
-        launch_timed(gemm16_kernel<false, false, true>, grid, dim3(256), s, true, true, a);
+        launch_timed(gemm16_kernel<false, false, true, false>, grid, dim3(256), s, true, true, a);
       }
       return hipGetLastError();
     }
@@ -1365,35 +1404,36 @@ hipError_t launch_gemm_nn(const GemmArgs& a, int tm, int tn, hipStream_t s) {
 namespace {
 template <bool NN>
 hipError_t launch_gemm_group(const GemmGroup& g, hipStream_t s) {
-  if (g.n <= 0 || g.n > kMaxGroup || g.off[0] != 0) return hipErrorInvalidValue;
+  if (g.n <= 0 || g.n > kMaxGroup || g.off[0] != 0 || g.hoff[0] != 0) return hipErrorInvalidValue;
+  bool fits = true;
+  int n_keep = 0;
   for (int p = 0; p < g.n; ++p) {
     const GemmArgs& a = g.a[p];
-    if (g.off[p + 1] - g.off[p] != a.n_mtiles * a.n_ntiles || a.sk_tiles != 0) return hipErrorInvalidValue;
+    if (g.off[p + 1] - g.off[p] != a.dp_tiles || g.hoff[p + 1] - g.hoff[p] != 2 * a.half_tiles || a.sk_tiles != 0 ||
+        (int64_t)a.dp_tiles + a.half_tiles != (int64_t)a.n_mtiles * a.n_ntiles)
+      return hipErrorInvalidValue;
+    fits = fits && (!NN || nn16_fits(a));
+    n_keep += a.keep != nullptr;
   }
-  if (g.off[g.n] <= 0) return hipSuccess;
-  if constexpr (!NN) {
-    // the masked instantiation serves launches whose projections all carry a mask
-    int n_keep = 0;
-    for (int p = 0; p < g.n; ++p) n_keep += g.a[p].keep != nullptr;
-    if (n_keep != 0 && n_keep != g.n) return hipErrorInvalidValue;
-    const bool drop = n_keep > 0;
-    if (drop) launch_timed(gemm16_group_kernel<true, false>, dim3((unsigned)g.off[g.n]), dim3(256), s, true, true, g);
-    else launch_timed(gemm16_group_kernel<false, false>, dim3((unsigned)g.off[g.n]), dim3(256), s, true, true, g);
-  } else {
-    bool fits = true, drop = false;
-    int n_keep = 0;
-    for (int p = 0; p < g.n; ++p) {
-      fits = fits && nn16_fits(g.a[p]);
-      n_keep += g.a[p].keep != nullptr;
+  const int32_t n_half = g.hoff[g.n];
+  if (g.off[g.n] + n_half <= 0) return hipSuccess;
+  // the masked instantiation serves launches whose projections all carry a mask
+  if (n_keep != 0 && n_keep != g.n) return hipErrorInvalidValue;
+  const bool drop = n_keep > 0;
+  const dim3 grid((unsigned)(g.off[g.n] + n_half));
+  if constexpr (NN) {
+    if (!fits) {  // the 8-wave form, for weights past 2^31 bytes
+      if (n_half > 0) return hipErrorInvalidValue;
+      launch_timed(gemm_group_kernel<NN>, grid, dim3(512), s, true, true, g);
+      return hipGetLastError();
     }
-    if (n_keep != 0 && n_keep != g.n) return hipErrorInvalidValue;
-    drop = n_keep > 0;
-    if (fits && drop)
-      launch_timed(gemm16_group_kernel<true, true>, dim3((unsigned)g.off[g.n]), dim3(256), s, true, true, g);
-    else if (fits)
-      launch_timed(gemm16_group_kernel<false, true>, dim3((unsigned)g.off[g.n]), dim3(256), s, true, true, g);
-    else
-      launch_timed(gemm_group_kernel<NN>, dim3((unsigned)g.off[g.n]), dim3(512), s, true, true, g);
+  }
+  if (n_half > 0) {
+    if (drop) launch_timed(gemm16_group_kernel<true, NN, true>, grid, dim3(256), s, true, true, g);
+    else launch_timed(gemm16_group_kernel<false, NN, true>, grid, dim3(256), s, true, true, g);
+  } else {
+    if (drop) launch_timed(gemm16_group_kernel<true, NN, false>, grid, dim3(256), s, true, true, g);
+    else launch_timed(gemm16_group_kernel<false, NN, false>, grid, dim3(256), s, true, true, g);
   }
   return hipGetLastError();
 }

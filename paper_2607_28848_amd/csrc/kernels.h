@@ -41,6 +41,7 @@ struct GemmArgs {
   // after the whole tiles.  Pieces write fp32 partials to sk_part (one tm * tn
   // slot per piece); a second kernel sums them and writes those tiles.
   int32_t dp_tiles, sk_tiles, sk_split;
+  int32_t half_tiles;    // instead of split tiles: the last half_tiles tiles run as two 128-row halves each
   float* sk_part;
   // dX under LoRA dropout: the prologue's low-rank term of row r, column c is
   // kept (times keep_scale) when bit c % 32 of keep[r][c / 32] is set, else
@@ -49,6 +50,10 @@ struct GemmArgs {
   int32_t keep_words;
   float keep_scale;
 };
+
+// The 16x16x32 NN form addresses the weight with 32-bit byte offsets from the
+// tile's first column, one K-step past the contraction at most.
+inline bool nn16_fits(const GemmArgs& a) { return ((int64_t)a.C + 64) * a.ldq * 2 < ((int64_t)1 << 31); }
 
 // Rank-r contraction of a few rows of one adapter (shrink h = x A^T, and
 // g = s dy B in the backward).
@@ -174,11 +179,13 @@ struct TokenReduceGroup {
   int32_t yoff[2 * kMaxGroup + 1];  // prefix of the kTokenCols-column blocks
   int32_t n;
 };
-// GEMM group: whole 256x256 tiles, workgroups [off[p], off[p+1]) take the
-// tiles of projection a[p] (XCD-major within the projection).
+// GEMM group: 256x256 tiles, workgroups [off[p], off[p+1]) take the first
+// dp_tiles tiles of projection a[p] (XCD-major within the projection), and the
+// workgroups behind them, [hoff[p], hoff[p+1]), the halves of its last half_tiles.
 struct GemmGroup {
   GemmArgs a[kMaxGroup];
   int32_t off[kMaxGroup + 1];
+  int32_t hoff[kMaxGroup + 1];
   int32_t n;
 };
 

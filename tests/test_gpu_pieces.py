@@ -110,3 +110,38 @@ def test_pieces_and_tiles_against_reference(T, Tt, K, N, r_max, ranks, wt):
                 print("  ids %s short %s " % (ids, short) + ", ".join("%s=%.1e" % kv for kv in errs.items()), flush=True)
                 for k, v in errs.items():
                     assert v <= TOL_BF16, (ids, short, k, v)
+
+
+@pytest.mark.parametrize("Tt", [3073, 3300])
+def test_half_tiles_match_whole_tiles(Tt):
+    """A last partial wave of 256 x 256 tiles run as 128-row halves (here 13 row tiles of 16
+    column tiles for Tt = 3073, 3300: a full wave is 256 tiles, so a group of two projections
+    leaves 160 tiles and a single N = 2048 forward takes halves only where they fill at most
+    half the CUs): the grouped results, whatever the launch's tail, are those of each
+    projection alone in a group with itself, bit for bit, and within the bar on the rows at
+    the halves' and tiles' edges."""
+    import torch
+    from paper_2607_28848_amd import dsv
+    segs = [(0, 200, 0, 1), (200, Tt - 300, 1, 1), (Tt - 100, 100, 2, 1)]
+    K, N = 1024, 4096
+    w = wl.custom(segs, [16, 8, 5], K=K, N=N, r_max=16, name="half")
+    w.projections = [wl.Projection("p", K, N)]
+    t = w.tensors(0, pad=np.nan)
+    d = {k: to_dev(t.store[k], "bf16") for k in ("X", "W", "A", "B", "dY")}
+    plan = dsv.segments_build(w.segments, w.n_tokens, w.ranks, w.scales, w.r_max, device="cuda")
+    outs = []
+    for n in (2, 3, 4):  # 416, 624 and 832 tiles: the tails are 160, 112 and 64 tiles
+        out = dsv.cobatch_fwd_grouped(plan, [(d["X"], d["W"], d["A"], d["B"])] * n)
+        grads = dsv.lora_bwd_grouped(plan, [(d["X"], d["W"], d["A"], d["B"], out[0][1], d["dY"])] * n)
+        torch.cuda.synchronize()
+        outs.append([o[0] for o in out] + [o[1] for o in out])
+        outs.append([g[2] for g in grads])
+    for group in (outs[0::2], outs[1::2]):
+        flat = [x for o in group for x in o if x.shape == group[0][0].shape]
+        assert all(torch.equal(_bits(x), _bits(flat[0])) for x in flat)
+    rows = np.unique(np.concatenate([np.arange(0, Tt, 211), [127, 128, 255, 256, 3071, 3072, Tt - 101, Tt - 1]]))
+    rows = rows.astype(np.int32)
+    Yr, _ = oracle_fwd(w, t, rows)
+    assert oracle.rel_err(to_host(outs[0][0])[rows], Yr) <= TOL_BF16
+    dXr = oracle_bwd(w, t, dx_rows=rows)[3]
+    assert oracle.rel_err(to_host(outs[1][0])[rows], dXr) <= TOL_BF16
