@@ -120,6 +120,17 @@ int dsv_segments_build(const dsv_segment* segs, int32_t n_segs, int32_t n_tokens
                        int32_t n_adapters, int32_t r_max, void* d_meta,
                        size_t* meta_bytes, void* hip_stream, dsv_plan** out_plan);
 
+/*
+ * dsv_plan_upload -- copies the packed blob of a plan that dsv_segments_build
+ * made without one (d_meta == NULL) to d_meta, asynchronously on hip_stream, so a
+ * caller can learn the blob's size and build the plan in one call.  d_meta:
+ * device memory, 256-byte aligned, meta_bytes of at least the size reported by
+ * dsv_segments_build, alive as long as the plan is used.  Returns DSV_ERR_ARG for a
+ * NULL or misaligned argument or a plan that is on the device already,
+ * DSV_ERR_SIZE when the buffer is too small, DSV_ERR_DEVICE when the copy fails.
+ */
+int dsv_plan_upload(dsv_plan* plan, void* d_meta, size_t meta_bytes, void* hip_stream);
+
 /* Number of training tokens T_t (rows of H_save, dY and dX); -1 if plan is NULL. */
 int32_t dsv_plan_train_rows(const dsv_plan* plan);
 

@@ -84,10 +84,8 @@ int build(const dsv_segment* segs, int32_t n_segs, int32_t T, const int32_t* ran
   std::vector<char> is_train(T, 0);
   for (int32_t i : order) {
     const dsv_segment& s = segs[i];
-    for (int32_t t = s.start; t < s.start + s.len; ++t) {
-      row_adapter[t] = s.adapter;
-      is_train[t] = (char)s.is_train;
-    }
+    std::fill(row_adapter.begin() + s.start, row_adapter.begin() + s.start + s.len, s.adapter);
+    std::fill(is_train.begin() + s.start, is_train.begin() + s.start + s.len, (char)s.is_train);
   }
   // Compact training order: ascending token row.
   std::vector<int32_t> train_rows, train_adapter;
@@ -103,10 +101,11 @@ int build(const dsv_segment* segs, int32_t n_segs, int32_t T, const int32_t* ran
 
   // Shrink work list: rows grouped by adapter (ascending row inside), split
   // into items of kRankItemRows rows; each item reads its adapter's A once.
-  std::vector<int32_t> shrink_rows(T);
-  std::iota(shrink_rows.begin(), shrink_rows.end(), 0);
-  std::stable_sort(shrink_rows.begin(), shrink_rows.end(),
-                   [&](int32_t x, int32_t y) { return row_adapter[x] < row_adapter[y]; });
+  // (counted by adapter: a comparison sort of the rows was most of the plan's time)
+  std::vector<int32_t> shrink_rows(T), next_row(n_ad + 1, 0);
+  for (int32_t t = 0; t < T; ++t) ++next_row[row_adapter[t] + 1];
+  for (int32_t a = 0; a < n_ad; ++a) next_row[a + 1] += next_row[a];
+  for (int32_t t = 0; t < T; ++t) shrink_rows[next_row[row_adapter[t]]++] = t;
   std::vector<int32_t> shrink_items;
   for (int32_t i = 0; i < T;) {
     int32_t a = row_adapter[shrink_rows[i]], j = i;
@@ -261,6 +260,8 @@ int build(const dsv_segment* segs, int32_t n_segs, int32_t T, const int32_t* ran
   // Pack.  Each array starts on a 64-word (256-byte) boundary.
   std::vector<int32_t>& m = p.meta;
   m.clear();
+  m.reserve((size_t)8 * T + shrink_items.size() + gather_items.size() + fwd_tiles.size() + fwd_tiles128.size() +
+            2 * bwd_tiles128.size() + 4 * (size_t)n_ad + 64 * 24);
   auto put = [&](const int32_t* src, size_t n) -> int64_t {
     m.resize((m.size() + 63) & ~size_t(63), 0);
     int64_t off = (int64_t)m.size();
@@ -307,6 +308,25 @@ int build(const dsv_segment* segs, int32_t n_segs, int32_t T, const int32_t* ran
   return DSV_OK;
 }
 
+// Starts the copy of the packed blob to d_meta.
+int upload(dsv_plan& p, void* d_meta, size_t bytes, void* hip_stream) {
+  const size_t need = (size_t)p.lay.total_words * sizeof(int32_t);
+  if (reinterpret_cast<uintptr_t>(d_meta) % 256 != 0) return DSV_ERR_ARG;
+  if (bytes < need) return DSV_ERR_SIZE;
+  hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  hipEvent_t ev = nullptr;
+  hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipMemcpyAsync(d_meta, p.meta.data(), need, hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) e = hipEventRecord(ev, st);
+  if (e != hipSuccess) {
+    if (ev) (void)hipEventDestroy(ev);
+    return DSV_ERR_DEVICE;
+  }
+  p.copy_done = ev;
+  p.d_meta = d_meta;
+  return DSV_OK;
+}
+
 }  // namespace
 
 extern "C" int dsv_segments_build(const dsv_segment* segs, int32_t n_segs, int32_t n_tokens,
@@ -332,28 +352,12 @@ extern "C" int dsv_segments_build(const dsv_segment* segs, int32_t n_segs, int32
   }
   const size_t need = (size_t)p->lay.total_words * sizeof(int32_t);
   if (d_meta) {
-    if (reinterpret_cast<uintptr_t>(d_meta) % 256 != 0) {
+    const int rc = upload(*p, d_meta, *meta_bytes, hip_stream);
+    if (rc != DSV_OK) {
+      if (rc == DSV_ERR_SIZE) *meta_bytes = need;
       delete p;
-      return DSV_ERR_ARG;
+      return rc;
     }
-    if (*meta_bytes < need) {
-      *meta_bytes = need;
-      delete p;
-      return DSV_ERR_SIZE;
-    }
-    hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    hipEvent_t ev = nullptr;
-    hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(d_meta, p->meta.data(), need, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipEventRecord(ev, st);
-    if (e != hipSuccess) {
-      if (ev) (void)hipEventDestroy(ev);
-      delete p;
-      return DSV_ERR_DEVICE;
-    }
-    p->copy_done = ev;
-    p->d_meta = d_meta;
   }
   *meta_bytes = need;
   if (out_plan)
@@ -361,6 +365,11 @@ extern "C" int dsv_segments_build(const dsv_segment* segs, int32_t n_segs, int32
   else
     delete p;
   return DSV_OK;
+}
+
+extern "C" int dsv_plan_upload(dsv_plan* p, void* d_meta, size_t meta_bytes, void* hip_stream) {
+  if (!p || !d_meta || p->d_meta) return DSV_ERR_ARG;
+  return upload(*p, d_meta, meta_bytes, hip_stream);
 }
 
 extern "C" int32_t dsv_plan_train_rows(const dsv_plan* p) { return p ? p->T_t : -1; }

@@ -13,6 +13,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Optional, Sequence
 
 import numpy as np
@@ -46,6 +47,8 @@ _f32p = ctypes.POINTER(ctypes.c_float)
 _lib.dsv_segments_build.argtypes = [_i32p, _i32, _i32, _i32p, _f32p, _i32, _i32, _vp,
                                     ctypes.POINTER(_sz), _vp, ctypes.POINTER(_vp)]
 _lib.dsv_segments_build.restype = ctypes.c_int
+_lib.dsv_plan_upload.argtypes = [_vp, _vp, _sz, _vp]
+_lib.dsv_plan_upload.restype = ctypes.c_int
 _lib.dsv_plan_train_rows.argtypes = [_vp]
 _lib.dsv_plan_train_rows.restype = _i32
 _lib.dsv_plan_train_row_index.argtypes = [_vp, _i32p]
@@ -94,25 +97,32 @@ class BwdProj(ctypes.Structure):
                 ("lddy", _i32), ("lddx", _i32), ("ldwt", _i32)]
 
 
+# The projection structs as packed bytes (the calls below marshal with these; the
+# library reads them during the call only).
+_FWD_PACK = struct.Struct("@ii6Piii4x").pack
+_BWD_PACK = struct.Struct("@ii10Piiiii4x").pack
+_ADAMW_PACK = struct.Struct("@ii10P").pack
+assert len(_FWD_PACK(*[0] * 11)) == ctypes.sizeof(FwdProj) and len(_BWD_PACK(*[0] * 17)) == ctypes.sizeof(BwdProj)
+
 _lib.dsv_row_stride.argtypes = [_i32, ctypes.c_int]
 _lib.dsv_row_stride.restype = _i32
 
 
 MAX_GROUP = 8
-_lib.dsv_cobatch_fwd_grouped_workspace.argtypes = [_vp, ctypes.c_int, _i32, ctypes.POINTER(FwdProj),
+_lib.dsv_cobatch_fwd_grouped_workspace.argtypes = [_vp, ctypes.c_int, _i32, _vp,
                                                    ctypes.POINTER(_sz)]
 _lib.dsv_cobatch_fwd_grouped_workspace.restype = ctypes.c_int
-_lib.dsv_cobatch_fwd_grouped.argtypes = [_vp, ctypes.c_int, _i32, ctypes.POINTER(FwdProj), _vp, _sz, _vp]
+_lib.dsv_cobatch_fwd_grouped.argtypes = [_vp, ctypes.c_int, _i32, _vp, _vp, _sz, _vp]
 _lib.dsv_cobatch_fwd_grouped.restype = ctypes.c_int
-_lib.dsv_lora_bwd_grouped_workspace.argtypes = [_vp, ctypes.c_int, _i32, ctypes.POINTER(BwdProj),
+_lib.dsv_lora_bwd_grouped_workspace.argtypes = [_vp, ctypes.c_int, _i32, _vp,
                                                 ctypes.POINTER(_sz)]
 _lib.dsv_lora_bwd_grouped_workspace.restype = ctypes.c_int
-_lib.dsv_lora_bwd_grouped.argtypes = [_vp, ctypes.c_int, _i32, ctypes.POINTER(BwdProj), _i32, _vp, _sz, _vp]
+_lib.dsv_lora_bwd_grouped.argtypes = [_vp, ctypes.c_int, _i32, _vp, _i32, _vp, _sz, _vp]
 _lib.dsv_lora_bwd_grouped.restype = ctypes.c_int
-_lib.dsv_cobatch_fwd_grouped_dropout.argtypes = [_vp, ctypes.c_int, _i32, ctypes.POINTER(FwdProj),
+_lib.dsv_cobatch_fwd_grouped_dropout.argtypes = [_vp, ctypes.c_int, _i32, _vp,
                                                  ctypes.POINTER(Dropout), _vp, _sz, _vp]
 _lib.dsv_cobatch_fwd_grouped_dropout.restype = ctypes.c_int
-_lib.dsv_lora_bwd_grouped_dropout.argtypes = [_vp, ctypes.c_int, _i32, ctypes.POINTER(BwdProj), _i32,
+_lib.dsv_lora_bwd_grouped_dropout.argtypes = [_vp, ctypes.c_int, _i32, _vp, _i32,
                                               ctypes.POINTER(Dropout), _vp, _sz, _vp]
 _lib.dsv_lora_bwd_grouped_dropout.restype = ctypes.c_int
 _lib.dsv_timing_enable.argtypes = [_i32]
@@ -134,7 +144,7 @@ class AdamWProj(ctypes.Structure):
         "dA", "dB", "A_master", "B_master", "A_m", "A_v", "B_m", "B_v", "A", "B")]
 
 
-_lib.dsv_adamw_step_grouped.argtypes = [_vp, ctypes.c_int, _i32, ctypes.POINTER(AdamWProj), _i32,
+_lib.dsv_adamw_step_grouped.argtypes = [_vp, ctypes.c_int, _i32, _vp, _i32,
                                         ctypes.POINTER(AdamWHparams), _vp]
 _lib.dsv_adamw_step_grouped.restype = ctypes.c_int
 _lib.dsv_gemm_config.argtypes = [_vp, ctypes.c_int, _i32, _i32, _i32, _i32p]
@@ -162,14 +172,14 @@ def lib_handle() -> ctypes.CDLL:
 
 
 def _stream_handle(stream):
+    """The HIP stream of a call: the given one, else torch's current one."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(int(stream.cuda_stream))
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return int(stream.cuda_stream)
 
 
-def _ptr(t) -> ctypes.c_void_p:
-    return ctypes.c_void_p(0 if t is None else int(t.data_ptr()))
+def _ptr(t) -> int:
+    return 0 if t is None else t.data_ptr()
 
 
 def row_stride(n: int, dtype_code: int = 0) -> int:
@@ -216,13 +226,11 @@ class Plan:
             _check(_lib.dsv_segments_build(*args, None, ctypes.byref(nbytes), None,
                                            ctypes.byref(self._h)), "dsv_segments_build")
         else:
-            import torch
-            _check(_lib.dsv_segments_build(*args, None, ctypes.byref(nbytes), None, None),
-                   "dsv_segments_build (size query)")
+            _check(_lib.dsv_segments_build(*args, None, ctypes.byref(nbytes), None,
+                                           ctypes.byref(self._h)), "dsv_segments_build")
             self.meta = torch.empty(max(int(nbytes.value), 256), dtype=torch.uint8, device=device)
-            _check(_lib.dsv_segments_build(*args, _ptr(self.meta), ctypes.byref(nbytes),
-                                           _stream_handle(stream), ctypes.byref(self._h)),
-                   "dsv_segments_build")
+            _check(_lib.dsv_plan_upload(self._h, _ptr(self.meta), nbytes, _stream_handle(stream)),
+                   "dsv_plan_upload")
         self.meta_bytes = int(nbytes.value)
 
     def __del__(self):
@@ -303,7 +311,7 @@ def _dropout(dropout):
         return None
     p, seed, offset = dropout[:3]
     mask = dropout[3] if len(dropout) > 3 else None
-    return Dropout(float(p), int(seed), int(offset), None if mask is None else ctypes.c_void_p(mask.data_ptr()))
+    return Dropout(float(p), int(seed), int(offset), None if mask is None else mask.data_ptr())
 
 
 def dropout_mask_words(plan: "Plan", K: int) -> int:
@@ -311,11 +319,11 @@ def dropout_mask_words(plan: "Plan", K: int) -> int:
     return plan.train_tokens * ((K + 31) // 32)
 
 
-def _workspace(nbytes, device, given):
-    import torch
+def _workspace(given, device, nbytes, *args):
+    """The caller's workspace, else one of nbytes(*args) bytes."""
     if given is not None:
         return given
-    return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+    return torch.empty(max(nbytes(*args), 256), dtype=torch.uint8, device=device)
 
 
 def cobatch_fwd(plan: Plan, X, W, A, B, Y=None, H_save=None, workspace=None, stream=None,
@@ -333,7 +341,7 @@ def cobatch_fwd(plan: Plan, X, W, A, B, Y=None, H_save=None, workspace=None, str
         Y = torch.empty((T, N), dtype=X.dtype, device=X.device)
     if H_save is None and plan.train_tokens > 0 and keep_h:
         H_save = torch.empty((plan.train_tokens, plan.r_max), dtype=X.dtype, device=X.device)
-    ws = _workspace(fwd_workspace_bytes(plan, dt, K, N), X.device, workspace)
+    ws = _workspace(workspace, X.device, fwd_workspace_bytes, plan, dt, K, N)
     d = _dropout(dropout)
     if d is None:
         _check(_lib.dsv_cobatch_fwd(plan.handle, dt, K, N, _ptr(X), _ptr(W), _ptr(A), _ptr(B), _ptr(Y),
@@ -378,7 +386,7 @@ def lora_bwd(plan: Plan, X, W, A, B, H_save, dY, dA=None, dB=None, dX=None, want
     if dX is None and want_dx and plan.train_tokens > 0:
         dX = torch.empty((plan.train_tokens, K), dtype=X.dtype, device=X.device)
     d = _dropout(dropout)
-    ws = _workspace(bwd_workspace_bytes(plan, dt, K, N, d is not None), X.device, workspace)
+    ws = _workspace(workspace, X.device, bwd_workspace_bytes, plan, dt, K, N, d is not None)
     if d is None:
         _check(_lib.dsv_lora_bwd(plan.handle, dt, K, N, _ptr(X), _ptr(W), _ptr(A), _ptr(B), _ptr(H_save),
                                  _ptr(dY), _ptr(dA), _ptr(dB), _ptr(dX if want_dx else None),
@@ -394,13 +402,13 @@ def lora_bwd(plan: Plan, X, W, A, B, H_save, dY, dA=None, dB=None, dX=None, want
 
 
 def _fwd_projs(items):
-    arr = (FwdProj * len(items))()
-    for i, (X, W, A, B, Y, H) in enumerate(items):
+    arr = []
+    for X, W, A, B, Y, H in items:
         K, N = X.shape[1], W.shape[0]
         _dense(A, B, H)
-        arr[i] = FwdProj(K, N, _ptr(X), _ptr(W), _ptr(A), _ptr(B), _ptr(Y), _ptr(H), _ld(X, K), _ld(W, K),
-                         _ld(Y, N))
-    return arr
+        arr.append(_FWD_PACK(K, N, _ptr(X), _ptr(W), _ptr(A), _ptr(B), _ptr(Y), _ptr(H), _ld(X, K), _ld(W, K),
+                             _ld(Y, N)))
+    return b"".join(arr)
 
 
 def fwd_grouped_workspace_bytes(plan: Plan, dtype_code: int, shapes) -> int:
@@ -451,8 +459,8 @@ def cobatch_fwd_grouped(plan: Plan, projs, workspace=None, stream=None, keep_h: 
             H = torch.empty((plan.train_tokens, plan.r_max), dtype=X.dtype, device=X.device)
         items.append((X, W, A, B, Y, H))
     dt = _dtype_code(items[0][0])
-    ws = _workspace(fwd_grouped_workspace_bytes(plan, dt, [(it[0].shape[1], it[1].shape[0]) for it in items]),
-                    items[0][0].device, workspace)
+    ws = _workspace(workspace, items[0][0].device, lambda: fwd_grouped_workspace_bytes(
+        plan, dt, [(it[0].shape[1], it[1].shape[0]) for it in items]))
     arr = _fwd_projs(items)
     dr = _dropouts(dropouts, len(items))
     if dr is None:
@@ -485,15 +493,16 @@ def lora_bwd_grouped(plan: Plan, projs, accumulate: bool = False, want_dx: bool 
             dX = torch.empty((plan.train_tokens, K), dtype=X.dtype, device=X.device)
         items.append((X, W, A, B, H, dY, dA, dB, dX if want_dx else None))
     dt = _dtype_code(items[0][0])
-    ws = _workspace(bwd_grouped_workspace_bytes(plan, dt, [(it[0].shape[1], it[1].shape[0]) for it in items]),
-                    items[0][0].device, workspace)
-    arr = (BwdProj * len(items))()
+    ws = _workspace(workspace, items[0][0].device, lambda: bwd_grouped_workspace_bytes(
+        plan, dt, [(it[0].shape[1], it[1].shape[0]) for it in items]))
+    arr = []
     for i, (X, W, A, B, H, dY, dA, dB, dX) in enumerate(items):
         Wt = wts[i] if wts is not None else None
         K, N = X.shape[1], W.shape[0]
         _dense(A, B, H, dA, dB)
-        arr[i] = BwdProj(K, N, _ptr(X), _ptr(W), _ptr(A), _ptr(B), _ptr(H), _ptr(dY), _ptr(dA), _ptr(dB), _ptr(dX),
-                         _ptr(Wt), _ld(X, K), _ld(W, K), _ld(dY, N), _ld(dX, K), _ld(Wt, N))
+        arr.append(_BWD_PACK(K, N, _ptr(X), _ptr(W), _ptr(A), _ptr(B), _ptr(H), _ptr(dY), _ptr(dA), _ptr(dB),
+                             _ptr(dX), _ptr(Wt), _ld(X, K), _ld(W, K), _ld(dY, N), _ld(dX, K), _ld(Wt, N)))
+    arr = b"".join(arr)
     dr = _dropouts(dropouts, len(items))
     if dr is None:
         _check(_lib.dsv_lora_bwd_grouped(plan.handle, dt, len(items), arr, 1 if accumulate else 0, _ptr(ws),
@@ -516,7 +525,7 @@ def adamw_step(plan: Plan, step: int, dA, dB, A_master, B_master, A_m, A_v, B_m,
     ref = A if A is not None else A_master
     code = BF16 if ref.dtype == torch.bfloat16 else F32
     hp = AdamWHparams(lr, beta1, beta2, eps, weight_decay)
-    ptr = lambda t: None if t is None else ctypes.c_void_p(t.data_ptr())  # noqa: E731
+    ptr = _ptr
     _check(_lib.dsv_adamw_step(plan.handle, code, K, N, step, ctypes.byref(hp), ptr(dA), ptr(dB),
                                ptr(A_master), ptr(B_master), ptr(A_m), ptr(A_v), ptr(B_m), ptr(B_v),
                                ptr(A), ptr(B), _stream_handle(stream)),
@@ -535,10 +544,9 @@ def adamw_grouped_prepared(plan: Plan, items, lr=1e-3, beta1=0.9, beta2=0.999, e
     """Marshal the arguments of dsv_adamw_step_grouped once; returns step(t), which
     only makes the call (for loops that repeat it over the same buffers)."""
     import torch
-    arr = (AdamWProj * len(items))()
+    arr = []
     code = None
-    ptr = lambda t: None if t is None else ctypes.c_void_p(t.data_ptr())  # noqa: E731
-    for i, it in enumerate(items):
+    for it in items:
         dA, dB, Am, Bm, mA, vA, mB, vB, A, B = it
         ref = A if A is not None else Am
         c = BF16 if ref.dtype == torch.bfloat16 else F32
@@ -546,9 +554,9 @@ def adamw_grouped_prepared(plan: Plan, items, lr=1e-3, beta1=0.9, beta2=0.999, e
             code = c
         elif c != code:
             raise ValueError("adamw_step_grouped: parameter copies of one dtype")
-        arr[i] = AdamWProj(Am.shape[2], Bm.shape[1], *[ptr(t) for t in (dA, dB, Am, Bm, mA, vA, mB, vB, A, B)])
+        arr.append(_ADAMW_PACK(Am.shape[2], Bm.shape[1], *map(_ptr, it)))
     hp = AdamWHparams(lr, beta1, beta2, eps, weight_decay)
-    args = (plan.handle, code if code is not None else BF16, len(items), arr)
+    args = (plan.handle, code if code is not None else BF16, len(items), b"".join(arr))
     tail = (ctypes.byref(hp), _stream_handle(stream))
 
     def step(t: int) -> None:
