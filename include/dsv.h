@@ -330,7 +330,8 @@ int dsv_lora_bwd_dropout(const dsv_plan* plan, dsv_dtype dtype, int32_t K, int32
  * compute for each entry; they return DSV_ERR_ARG for a NULL dropouts and
  * DSV_ERR_RANGE for any p outside [0, 1), and use the same workspace sizes.
  *
- * Streams (the grouped bf16 backward of two or more projections): dX needs g
+ * Streams (the grouped bf16 backward of two or more projections whose dX runs
+ * in tiles; with pieces everything stays on hip_stream): dX needs g
  * only, so the dA reductions and the final sums of dA and dB run beside the dX GEMMs
  * on a second stream of the current device that the library creates on first
  * use (default priority, non-blocking, kept until the process ends), so

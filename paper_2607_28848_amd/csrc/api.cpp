@@ -1702,8 +1702,11 @@ int bwd_grouped_impl(const dsv_plan* p, dsv_dtype dt, int32_t n_proj, const dsv_
   };
 
   // dX needs g only: the dA reduction and the final sums run beside it on the
-  // side stream (joined back into the caller's stream before the call returns)
-  {
+  // side stream (joined back into the caller's stream before the call returns).
+  // Not beside pieces: those are short and fill every CU's LDS, so the side work
+  // waits for them anyway (256 rows through gate and up: 118.6 us forked here, 127
+  // with dB and g on the side stream as well, 113.7 on one stream).
+  if (!(pp.use && workspace_bytes - total >= pp.bytes)) {
     std::lock_guard<std::mutex> lk(g_side_mu);
     if (SideStream* sd = side_stream()) {
       if (hipEventRecord(sd->fork, s) != hipSuccess) return DSV_ERR_DEVICE;
