@@ -152,6 +152,11 @@ __device__ __forceinline__ void shrink_piece(const PartShrink& g, const PartGrou
 //   LDS image, contraction-contiguous tiles (128-byte rows): 16-byte chunk c
 //   of row r in slot c ^ (r ^ r/8) % 8; NN weight tile ([64][TN]): chunk c of
 //   row n in slot c ^ 2(n % 4), read back with ds_read_b64_tr_b16.
+// Decode is bound by the stream of W: the tiles keep about 12 MB of it in flight
+// over the chip (T = 64, 4096 x 28672: 41 us, 5.7 TB/s; with 256 x 256 tiles 101).
+// A few hundred rows are bound by the latency of a K-step, hence the buffers: a
+// 128 x 128 workgroup takes 0.98 us per K-step with two, 0.41 with four (365 rows,
+// 4096 x 4096: 22 us, before 45); 128 x 256 reads a quarter less per product.
 // Accumulators: weight fragment first, so acc[i][j][v] is output row
 // 16i + lane%16, column 16j + 4(lane/16) + v of the wave's part.
 // ---------------------------------------------------------------------------

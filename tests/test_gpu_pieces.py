@@ -114,12 +114,11 @@ def test_pieces_and_tiles_against_reference(T, Tt, K, N, r_max, ranks, wt):
 
 @pytest.mark.parametrize("Tt", [3073, 3300])
 def test_half_tiles_match_whole_tiles(Tt):
-    """A last partial wave of 256 x 256 tiles run as 128-row halves (here 13 row tiles of 16
-    column tiles for Tt = 3073, 3300: a full wave is 256 tiles, so a group of two projections
-    leaves 160 tiles and a single N = 2048 forward takes halves only where they fill at most
-    half the CUs): the grouped results, whatever the launch's tail, are those of each
-    projection alone in a group with itself, bit for bit, and within the bar on the rows at
-    the halves' and tiles' edges."""
+    """A last partial wave of 256 x 256 tiles run as 128-row halves: 13 row tiles (the last
+    one ends in its first half, or in its second) by 16 column tiles per projection, so
+    groups of 2, 3 and 4 leave 160, 112 and 64 tiles of a 256-CU wave: whole, halved and
+    halved.  Every projection's Y, h and dX are the same bits in each group, and within the
+    bar on rows at the halves' and tiles' edges."""
     import torch
     from paper_2607_28848_amd import dsv
     segs = [(0, 200, 0, 1), (200, Tt - 300, 1, 1), (Tt - 100, 100, 2, 1)]
@@ -130,7 +129,7 @@ def test_half_tiles_match_whole_tiles(Tt):
     d = {k: to_dev(t.store[k], "bf16") for k in ("X", "W", "A", "B", "dY")}
     plan = dsv.segments_build(w.segments, w.n_tokens, w.ranks, w.scales, w.r_max, device="cuda")
     outs = []
-    for n in (2, 3, 4):  # 416, 624 and 832 tiles: the tails are 160, 112 and 64 tiles
+    for n in (2, 3, 4):
         out = dsv.cobatch_fwd_grouped(plan, [(d["X"], d["W"], d["A"], d["B"])] * n)
         grads = dsv.lora_bwd_grouped(plan, [(d["X"], d["W"], d["A"], d["B"], out[0][1], d["dY"])] * n)
         torch.cuda.synchronize()
