@@ -109,22 +109,27 @@ GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool al
 //   tiles    the 128 x 128 form's rounds at 1.0 us per K-step (0.45 with one
 //            workgroup per CU) or the 256 x 256 form's at 1.4 us (half tiles: 0.7 of
 //            it; a split last round and its sum: 1/split of it and the pieces'
-//            bytes); gathered rows cost another launch
+//            bytes)
 // Fitted to timings of M = 8 .. 2048 rows of the Llama-3-8B shapes on MI355X:
 // the pieces win below about 500 rows (M = 96, N = K = 4096: 19.0 against 32.5
 // us; M = 256, K = 14336: 50.9 against 59.3), the tiles above (M = 1500, K = N =
 // 4096: 57.9 against 71.0), where only a clear gain takes the pieces.  Up to
 // kPartRows rows the pieces are taken whatever the estimate: they won or tied at
 // every shape timed, and so a group's projections all run in pieces or none does.
+// A forward's choice depends on the number of rows and the shapes, never on how the
+// rows are grouped into segments (the launch that gathered rows cost the tiles, about
+// 6 us, is left out for that): the base product of a row is the same bits in every
+// table of as many rows.
 struct PartPlan {
   bool use = false;
   int cfg = 0;
   int32_t n_m[kMaxGroup] = {}, n_n[kMaxGroup] = {}, split[kMaxGroup] = {};
   size_t off[kMaxGroup] = {}, bytes = 0;  // the pieces' buffers, past the rest of the workspace
   size_t h_off[kMaxGroup] = {};           // forward: the shrink's pieces
+  size_t bytes_any = 0;                   // forward: the most `bytes` of any grouping of the rows
 };
 constexpr int kMinPartSteps = 4, kPartRows = 256;
-constexpr double kPartBytesPerUs = 5e6, kWeightBytesPerUs = 5.5e6, kSumUs = 4.0, kGatherUs = 6.0, kTileStepUs = 1.4;
+constexpr double kPartBytesPerUs = 5e6, kWeightBytesPerUs = 5.5e6, kSumUs = 4.0, kTileStepUs = 1.4;
 
 double tiles_us(const GemmPlan& g, int32_t C) {
   const int64_t cus = device_cus(), nk = (C + 63) / 64;
@@ -181,12 +186,15 @@ PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout,
       best.n_m[i] = (M + kPartCfg[best.cfg].tm - 1) / kPartCfg[best.cfg].tm;
       best.n_n[i] = (Nout[i] + kPartCfg[best.cfg].tn - 1) / kPartCfg[best.cfg].tn;
       best.off[i] = best.bytes;
-      best.bytes += align256((size_t)best.split[i] * M * Nout[i] * 4);
+      const size_t part = align256((size_t)best.split[i] * M * Nout[i] * 4);
+      best.bytes += part;
       if (!p) continue;
       int32_t pieces, cpp;
       skinny_split(C[i], p->n_shrink, &pieces, &cpp);
       best.h_off[i] = best.bytes;
       best.bytes += align256((size_t)pieces * M * p->r_max * 4);
+      skinny_split(C[i], (M + kRankItemRows - 1) / kRankItemRows, &pieces, &cpp);  // the fewest items: the most pieces
+      best.bytes_any += part + align256((size_t)pieces * M * p->r_max * 4);
     }
   return best;
 }
@@ -271,7 +279,7 @@ GemmPlan bwd_gemm_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
 // Pieces or tiles of one projection's forward / dX GEMM.
 PartPlan fwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N, bool allow_split = true) {
   if (dt != DSV_BF16 || p.T == 0) return PartPlan{};
-  return part_plan(&p, p.T, 1, &N, &K, tiles_us(fwd_gemm_plan(p, dt, K, N, allow_split), K) + (p.n_gather > 0 ? kGatherUs : 0.0));
+  return part_plan(&p, p.T, 1, &N, &K, tiles_us(fwd_gemm_plan(p, dt, K, N, allow_split), K));
 }
 PartPlan bwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
   if (dt != DSV_BF16 || p.T_t == 0) return PartPlan{};
@@ -295,7 +303,7 @@ PartPlan group_part_plan(const dsv_plan& p, int pass, int32_t n, const Proj* pr,
   }
   // tiles in rounds over the CUs, the longest contraction setting the round
   const double rounds = steps / cus / longest, part = rounds - std::floor(rounds);
-  const double whole = (std::floor(rounds) + (part > 0.5 ? 1.0 : part > 0.0 ? 0.7 : 0.0)) * longest * kTileStepUs + (pass == 0 && p.n_gather > 0 ? kGatherUs : 0.0);
+  const double whole = (std::floor(rounds) + (part > 0.5 ? 1.0 : part > 0.0 ? 0.7 : 0.0)) * longest * kTileStepUs;
   const PartPlan pp = part_plan(pass == 0 ? &p : nullptr, M, n, Nout, C, whole);
   for (int i = 0; pp.use && i < n; ++i)
     if (!(pass == 0 ? fwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N) : bwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N)).sk_tiles &&
@@ -659,9 +667,9 @@ void add_part_shrink(const dsv_plan& p, PartGroup& pg, FinishGroup& fg, const Pa
 }
 
 // noalloc: the allocation-free form (dsv_cobatch_fwd_noalloc): the workspace is
-// the library's device scratch, the GEMM plan splits no tile along the
-// contraction (a split needs a partial tile per piece, tens of MB), and no
-// benchmark timing events are created.
+// the library's device scratch, the GEMM plan splits no 256 x 256 tile along the
+// contraction (a split needs a partial tile per piece, tens of MB; batches of few
+// rows run in pieces where those fit), and no benchmark timing events are created.
 int fwd_impl(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N, const void* X, const void* W, const void* A,
              const void* B, void* Y, void* H_save, const dsv_dropout* drop, void* workspace,
              size_t workspace_bytes, void* hip_stream, const Strides* lds = nullptr, bool noalloc = false) {
@@ -758,16 +766,18 @@ int fwd_impl(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N, const void* 
   sk.split_items = p->n_shrink;
   // 1a. few rows: the base product in pieces, the shrink beside them (a launch of
   //     its own where dropout masks it), then their sum with the low-rank term of
-  //     every row.  A workspace without room for the pieces takes the tiles.
+  //     every row.  A workspace without room for the pieces takes the tiles.  The
+  //     fixed scratch of the allocation-free form has room or not for any grouping of
+  //     the rows alike: its pieces need none of the other regions (no dropout there).
   const PartPlan pp = fwd_part_plan(*p, dt, K, N, !noalloc);
-  const bool pieces = pp.use && workspace_bytes >= ws.total && workspace_bytes - ws.total >= pp.bytes;
-  if (pieces) {
+  char* parts = at<char>(workspace, noalloc ? 0 : ws.total);
+  if (pp.use && (noalloc ? workspace_bytes >= pp.bytes_any : workspace_bytes - ws.total >= pp.bytes)) {
     if (keep && launch_shrink(sk, p->n_shrink, p->r_used, s) != hipSuccess) return DSV_ERR_DEVICE;
     PartGroup pg{};
     FinishGroup fg = fwd_finish(*p);
     add_part(pg, fg, pp, 0, PartArgs{static_cast<const uint16_t*>(X), ld.x, static_cast<const uint16_t*>(W), ld.w, p->T, N, K},
-             at<char>(workspace, ws.total), h_all, ldh, B, Y, ld.y, nullptr, 0, 1.f);
-    if (!keep) add_part_shrink(*p, pg, fg, pp, 0, A, at<char>(workspace, ws.total), H_save);
+             parts, h_all, ldh, B, Y, ld.y, nullptr, 0, 1.f);
+    if (!keep) add_part_shrink(*p, pg, fg, pp, 0, A, parts, H_save);
     const int tk = noalloc ? -1 : timing_begin(0, s);
     e = launch_part_gemm(pg, pp.cfg, p->r_used, false, s);
     if (e == hipSuccess) e = launch_part_finish(fg, p->n_shrink, p->r_used, false, s);

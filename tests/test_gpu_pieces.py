@@ -144,3 +144,27 @@ def test_half_tiles_match_whole_tiles(Tt):
     assert oracle.rel_err(to_host(outs[0][0])[rows], Yr) <= TOL_BF16
     dXr = oracle_bwd(w, t, dx_rows=rows)[3]
     assert oracle.rel_err(to_host(outs[1][0])[rows], dXr) <= TOL_BF16
+
+
+@pytest.mark.parametrize("T,K,N", [(705, 4096, 4096), (400, 4096, 14336), (320, 1024, 1024)])
+def test_zero_B_is_the_same_base_whatever_the_grouping(T, K, N):
+    """B = 0: Y is the same bits for one segment (nothing gathered), for every row on its own
+    (all gathered) and for a mix, in the ordinary and the allocation-free forward, at sizes
+    near the line between pieces and tiles."""
+    import torch
+    from paper_2607_28848_amd import dsv
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    X, W, A = (torch.randn(s, generator=gen, device="cuda").bfloat16() for s in ((T, K), (N, K), (3, 16, K)))
+    B = torch.zeros((3, N, 16), dtype=torch.bfloat16, device="cuda")
+    tables = [[(0, T, 0, 0)], [(t, 1, t % 3, 0) for t in range(T)], [(0, 1, 2, 0), (1, 150, 1, 1), (151, T - 151, 0, 0)]]
+    outs = {"fwd": [], "noalloc": []}
+    for segs in tables:
+        plan = dsv.segments_build(segs, T, [16, 8, 16], [2.0] * 3, 16, device="cuda")
+        print("T=%d K=%d N=%d gathered %d: %s" % (T, K, N, plan.counts()["gathered_rows"],
+                                                  dsv.gemm_config(plan, dsv.BF16, K, N, 0)), flush=True)
+        outs["fwd"].append(dsv.cobatch_fwd(plan, X, W, A, B)[0])
+        outs["noalloc"].append(dsv.cobatch_fwd_noalloc(plan, X, W, A, B)[0])
+    torch.cuda.synchronize()
+    for ys in outs.values():
+        assert all(torch.equal(_bits(y), _bits(ys[0])) for y in ys[1:])
+        assert oracle.rel_err(to_host(ys[0][::37]), to_host(X[::37]) @ to_host(W).T) <= TOL_BF16

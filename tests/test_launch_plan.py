@@ -1,0 +1,116 @@
+"""Which kernels a call launches, on the CPU: the library's host code is built with the
+launchers and the HIP calls replaced by stubs that write down each launch
+(launch_recorder.cpp) for a device of 256 compute units, and called through the binding
+with addresses that nothing reads."""
+import ctypes
+import importlib.util
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2607_28848_amd import build as pkg_build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+BUF = 1 << 30   # an operand's address
+WS = 1 << 40    # the workspace's
+SCRATCH = 64 << 20
+
+
+class Recorded:
+    """The binding on the recording library: call(fn) -> (status, launches)."""
+
+    def __init__(self, path):
+        old = os.environ.get("DSV_LIBRARY")
+        os.environ["DSV_LIBRARY"] = path
+        try:
+            spec = importlib.util.spec_from_file_location("dsv_recorded", os.path.join(pkg_build.PKG, "dsv.py"))
+            self.dsv = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(self.dsv)
+        finally:
+            if old is None:
+                del os.environ["DSV_LIBRARY"]
+            else:
+                os.environ["DSV_LIBRARY"] = old
+        self.lib = self.dsv.lib_handle()
+        self.lib.recorder_log.restype = ctypes.c_char_p
+        self.lib.recorder_scratch.restype = ctypes.c_void_p
+
+    def plan(self, segs, ranks, r_max):
+        p = self.dsv.segments_build(segs, sum(s[1] for s in segs), ranks, [2.0] * len(ranks), r_max)
+        assert self.lib.dsv_plan_upload(p.handle, WS, p.meta_bytes, None) == self.dsv.OK
+        return p
+
+    def call(self, fn, *args):
+        self.lib.recorder_clear()
+        rc = fn(*args)
+        out = []
+        for l in self.lib.recorder_log().decode().splitlines():
+            kind, *kv = l.split()
+            out.append(dict({"kind": kind}, **{k: int(v) for k, v in (x.split("=") for x in kv)}))
+        return rc, out
+
+    def fwd(self, p, K, N, dtype=0):
+        n = self.dsv.fwd_workspace_bytes(p, dtype, K, N)
+        return self.call(self.lib.dsv_cobatch_fwd, p.handle, dtype, K, N, BUF, BUF, BUF, BUF, BUF, BUF, WS, n, None)
+
+    def noalloc(self, p, K, N):
+        return self.call(self.lib.dsv_cobatch_fwd_noalloc, p.handle, 0, K, N, BUF, BUF, BUF, BUF, BUF, BUF, None)
+
+    def fwd_grouped(self, p, shapes):
+        n = self.dsv.fwd_grouped_workspace_bytes(p, 0, shapes)
+        pr = b"".join(self.dsv._FWD_PACK(K, N, BUF, BUF, BUF, BUF, BUF, BUF, 0, 0, 0) for K, N in shapes)
+        return self.call(self.lib.dsv_cobatch_fwd_grouped, p.handle, 0, len(shapes), pr, WS, n, None)
+
+
+@pytest.fixture(scope="module")
+def rec(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("rec") / "librecorded.so")
+    srcs = [os.path.join(pkg_build.CSRC, s) for s in pkg_build.HOST_SOURCES] + [os.path.join(HERE, "launch_recorder.cpp")]
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__",
+                    "-I", os.path.join(pkg_build.ROCM, "include"), "-I", os.path.join(pkg_build.ROOT, "include"),
+                    "-Wl,-Bsymbolic", "-Wl,--no-undefined", "-o", so] + srcs, check=True)
+    return Recorded(so)
+
+
+def _base(launches):
+    """How the base product is summed: its launches without addresses and without the shrink."""
+    return [tuple((k, v) for k, v in l.items() if k not in ("shrink", "part", "h_part", "h_bytes"))
+            for l in launches if re.match("part|gemm|group", l["kind"])]
+
+
+@pytest.mark.parametrize("K,N", [(4096, 4096), (4096, 14336), (14336, 4096), (1024, 1024), (520, 776)])
+def test_base_product_does_not_depend_on_the_grouping(rec, K, N):
+    """Tables of as many rows, one segment or every row on its own (all gathered), sum the
+    base product alike in every forward: with B = 0 their results are then the same bits."""
+    refused = 0
+    for T in list(range(1, 258, 37)) + list(range(260, 1400, 29)):
+        a = rec.plan([(0, T, 0, 0)], [16, 16], 16)
+        b = rec.plan([(t, 1, t % 2, 0) for t in range(T)], [16, 16], 16)
+        assert b.counts()["gathered_rows"] == T
+        for what, call in (("single", lambda p: rec.fwd(p, K, N)), ("noalloc", lambda p: rec.noalloc(p, K, N)),
+                           ("group", lambda p: rec.fwd_grouped(p, [(K, N), (K, 8 * (N // 16))]))):
+            (ra, la), (rb, lb) = call(a), call(b)
+            if what == "noalloc" and rec.dsv.ERR_SIZE in (ra, rb):
+                refused += 1  # the gathered rows' terms alone exceed the scratch
+                continue
+            assert ra == rb == rec.dsv.OK
+            assert _base(la) and _base(la) == _base(lb), (what, T, la, lb)
+    assert refused < 40
+
+
+def test_noalloc_pieces_stay_inside_the_scratch(rec):
+    """Pieces of the allocation-free forward lie within the 64 MiB scratch, however the
+    rows are grouped, up to the largest that fit."""
+    base, most = rec.lib.recorder_scratch(), 0
+    for K, N in ((4096, 4096), (4096, 14336), (14336, 4096), (8192, 28672)):
+        for T in (1, 33, 200, 256, 292, 365, 480, 1300):
+            for p in (rec.plan([(0, T, 0, 0)], [64], 64), rec.plan([(t, 1, t % 2, 0) for t in range(T)], [64] * 2, 64)):
+                rc, launches = rec.noalloc(p, K, N)
+                for l in launches:
+                    if l["kind"] == "part":
+                        ends = [l["part"] + l["bytes"] - base, l["h_part"] + l["h_bytes"] - base]
+                        assert l["part"] >= base and l["h_part"] >= base and max(ends) <= SCRATCH, (K, N, T, l)
+                        most = max(most, *ends)
+    assert most > SCRATCH // 2
