@@ -100,22 +100,28 @@ GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool al
   return p;
 }
 
-// GEMM in pieces (launch_part_gemm) for a batch's projections, or the tile
-// kernels above: both are costed in microseconds and the smaller cost wins.
-//   pieces   rounds of workgroups over the CUs times K-steps per piece times the
-//            configuration's time per step (at least the weights at 5.5 TB/s),
-//            plus the fp32 pieces written and read once each at 5 TB/s and the
-//            launch that sums them
-//   tiles    the 128 x 128 form's rounds at 1.0 us per K-step (0.45 with one
-//            workgroup per CU) or the 256 x 256 form's at 1.4 us (half tiles: 0.7 of
-//            it; a split last round and its sum: 1/split of it and the pieces'
-//            bytes)
-// Fitted to timings of M = 8 .. 2048 rows of the Llama-3-8B shapes on MI355X:
-// the pieces win below about 500 rows (M = 96, N = K = 4096: 19.0 against 32.5
-// us; M = 256, K = 14336: 50.9 against 59.3), the tiles above (M = 1500, K = N =
-// 4096: 57.9 against 71.0), where only a clear gain takes the pieces.  Up to
-// kPartRows rows the pieces are taken whatever the estimate: they won or tied at
-// every shape timed, and so a group's projections all run in pieces or none does.
+// GEMM in pieces (launch_part_gemm) for a batch's projections, or the tile kernels
+// above.  Of the pieces' forms the one with the smallest cost is taken: rounds of
+// workgroups over the CUs times K-steps per piece times the configuration's time per
+// step (at least the weights at 5.5 TB/s), plus the fp32 pieces written and read once
+// each at 5 TB/s.  Then its whole time is estimated beside that of the tiles, and the
+// smaller one wins.  Both estimates were fitted to about 20000 calls timed both ways
+// on MI355X, single and groups of two and three, forward and backward, 1 .. 2400 rows,
+// K and N from 64 to 16384 and 131072, one segment:
+//   tiles    (kTileStep us per K-step + kTileEnd) per round of the form, the second
+//            number for a half tile, a split round and its sum: kSplitSum and the fp32
+//            pieces at 13 TB/s more; at least the weights at 3.4 .. 5.2 TB/s and the
+//            output at 2.1; in the forward the shrink's read of X at 3.6
+//   pieces   per step and round kPieceStep and kPieceEnd, at least the weights at 5 .. 6
+//            TB/s; 2.5 us per 2^20 fp32 elements of the pieces written and summed, and
+//            kPieceSum more than the tiles for the launch that sums them
+// The forward's pieces must be 4% ahead, above kPartRows rows any pieces 10% (there a
+// wrong guess costs most).  Of the fitted calls, the choice is the slower by more than
+// 3% and 0.3 us, pieces where tiles were faster, in 0.6% of the single and 0.7% of the
+// grouped forwards' pieces and 7% (2 us of 30, short contractions) and 0.1% of the
+// backwards'; at the Llama projections by 12% at most.
+//   K = N = 4096, 8 rows: 12 us in pieces, 38 in tiles; K = 1024, N = 32768, 128 rows:
+//   34 and 23, so tiles; K = 4096, N = 14336, 304 rows: 69 and 58, so tiles
 // A forward's choice depends on the number of rows and the shapes, never on how the
 // rows are grouped into segments (the launch that gathered rows cost the tiles, about
 // 6 us, is left out for that): the base product of a row is the same bits in every
@@ -128,17 +134,29 @@ struct PartPlan {
   size_t h_off[kMaxGroup] = {};           // forward: the shrink's pieces
   size_t bytes_any = 0;                   // forward: the most `bytes` of any grouping of the rows
 };
-constexpr int kMinPartSteps = 4, kPartRows = 256;
-constexpr double kPartBytesPerUs = 5e6, kWeightBytesPerUs = 5.5e6, kSumUs = 4.0, kTileStepUs = 1.4;
+constexpr int kMinPartSteps = 4, kPartRows = 1024;
+constexpr double kPartBytesPerUs = 5e6, kWeightBytesPerUs = 5.5e6;
+// 128 x 128 tiles with one workgroup per CU, with two, 256 x 256 tiles
+constexpr double kTileStep[3] = {0.6, 0.98, 1.5}, kTileEnd[3] = {4.4, 5.2, 7.4}, kTileWeightBytesPerUs[3] = {3.7e6, 5.2e6, 3.4e6}, kFullWeightBytesPerUs = 4.2e6;
+constexpr double kHalfStep = 0.81, kSplitSum = 20.0, kSplitBytesPerUs = 13e6, kOutBytesPerUs = 2.1e6, kShrinkBytesPerUs = 3.6e6;
+constexpr double kPieceStep[kPartCfgs] = {0.21, 0.47, 0.56, 0.89}, kPieceEnd[kPartCfgs] = {0.65, 0.55, 1.2, 0.0};
+constexpr double kPieceWeightBytesPerUs[kPartCfgs] = {6.0e6, 5.8e6, 5.0e6, 5.0e6}, kPieceElemUs = 2.5e-6, kPieceSum = 2.7, kFwdMargin = 0.96, kRowsMargin = 0.9;
 
-double tiles_us(const GemmPlan& g, int32_t C) {
+// Time of a tiles' launch at least: its weights and output.
+double stream_us(double weight_bytes_per_us, int32_t M, int32_t Nout, int32_t C) {
+  return 2.0 * Nout * C / weight_bytes_per_us + 2.0 * M * Nout / kOutBytesPerUs;
+}
+double tiles_us(const GemmPlan& g, int32_t M, int32_t Nout, int32_t C) {
   const int64_t cus = device_cus(), nk = (C + 63) / 64;
   if (cus <= 0) return 0.0;  // no device: no launch plan either
-  if (g.tm == 128) return g.dp_tiles <= cus ? nk * 0.45 : (double)((g.dp_tiles + 2 * cus - 1) / (2 * cus)) * nk;
-  double t = ((double)((g.dp_tiles + cus - 1) / cus) + (g.half_tiles > 0 ? 0.7 : 0.0)) * nk * kTileStepUs;
+  const int form = g.tm == 256 ? 2 : g.dp_tiles <= cus ? 0 : 1;
+  const int64_t per = form == 1 ? 2 * cus : cus;
+  double t = (double)((g.dp_tiles + per - 1) / per) * (kTileStep[form] * nk + kTileEnd[form]);
+  if (g.half_tiles > 0) t += kHalfStep * nk + kTileEnd[2];
   if (g.sk_tiles > 0)
-    t += kTileStepUs * nk / g.sk_split + kSumUs + (double)g.sk_tiles * g.sk_split * g.tm * g.tn * 8 / kPartBytesPerUs;
-  return t;
+    t += kTileStep[2] * nk / g.sk_split + kSplitSum + (double)g.sk_tiles * g.sk_split * g.tm * g.tn * 8 / kSplitBytesPerUs;
+  const bool full = form == 2 && g.dp_tiles >= cus;  // tiles on every CU draw more
+  return std::max(t, stream_us(full ? kFullWeightBytesPerUs : kTileWeightBytesPerUs[form], M, Nout, C));
 }
 
 // p (forward): the plan whose shrink runs beside the pieces.
@@ -147,14 +165,15 @@ PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout,
   const int cus = device_cus();
   if (cus <= 0 || M <= 0) return best;
   static const int kSplits[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
-  double w_us = 0, t_best = M <= kPartRows ? HUGE_VAL : (M > 512 ? 0.85 * t_tiles : t_tiles) - kSumUs;
+  double w_bytes = 0, x_bytes = 0, w_us, piece_us = 0, t_best = HUGE_VAL;
   int32_t nk[kMaxGroup], nk_max = 1;
   for (int i = 0; i < n; ++i) {
     nk[i] = (C[i] + 63) / 64;
-    w_us += 2.0 * Nout[i] * C[i] / kWeightBytesPerUs;
+    w_bytes += 2.0 * Nout[i] * C[i];
+    x_bytes += 2.0 * M * C[i];
     nk_max = std::max(nk_max, nk[i]);
   }
-  if (w_us >= t_best) return best;
+  w_us = w_bytes / kWeightBytesPerUs;
   for (int cfg = 0; cfg < kPartCfgs; ++cfg) {
     const PartCfg& pc = kPartCfg[cfg];
     if (pc.tm < 64 && M > pc.tm) continue;  // the 32-row tile is for batches of one row tile
@@ -171,16 +190,19 @@ PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout,
         elems += sp * M * Nout[i];
       }
       if (wgs > INT32_MAX) break;
-      const double us = std::max((double)((wgs + slots - 1) / slots * t) * pc.step_us, w_us) +
-                        (double)elems * 8 / kPartBytesPerUs;
+      const int64_t rounds = (wgs + slots - 1) / slots;
+      const double us = std::max((double)(rounds * t) * pc.step_us, w_us) + (double)elems * 8 / kPartBytesPerUs;
       if (us < t_best) {
         t_best = us;
-        best.use = true;
         best.cfg = cfg;
+        piece_us = std::max(rounds * (kPieceStep[cfg] * t + kPieceEnd[cfg]), w_bytes / kPieceWeightBytesPerUs[cfg]) +
+                   kPieceElemUs * elems + kPieceSum;
         for (int i = 0; i < n; ++i) best.split[i] = (nk[i] + t - 1) / t;
       }
     }
   }
+  if (M > kPartRows) t_tiles *= kRowsMargin;
+  best.use = piece_us > 0 && piece_us < (p ? kFwdMargin * (t_tiles + x_bytes / kShrinkBytesPerUs) : t_tiles);
   if (best.use)
     for (int i = 0; i < n; ++i) {
       best.n_m[i] = (M + kPartCfg[best.cfg].tm - 1) / kPartCfg[best.cfg].tm;
@@ -279,11 +301,11 @@ GemmPlan bwd_gemm_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
 // Pieces or tiles of one projection's forward / dX GEMM.
 PartPlan fwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N, bool allow_split = true) {
   if (dt != DSV_BF16 || p.T == 0) return PartPlan{};
-  return part_plan(&p, p.T, 1, &N, &K, tiles_us(fwd_gemm_plan(p, dt, K, N, allow_split), K));
+  return part_plan(&p, p.T, 1, &N, &K, tiles_us(fwd_gemm_plan(p, dt, K, N, allow_split), p.T, N, K));
 }
 PartPlan bwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
   if (dt != DSV_BF16 || p.T_t == 0) return PartPlan{};
-  return part_plan(nullptr, p.T_t, 1, &K, &N, tiles_us(bwd_gemm_plan(p, dt, K, N), N));
+  return part_plan(nullptr, p.T_t, 1, &K, &N, tiles_us(bwd_gemm_plan(p, dt, K, N), p.T_t, K, N));
 }
 // ... of a grouped call, whose tiles share one launch of whole 256 x 256 tiles.
 // A projection whose single call splits no contraction keeps its whole tiles
@@ -294,17 +316,19 @@ PartPlan group_part_plan(const dsv_plan& p, int pass, int32_t n, const Proj* pr,
   const int cus = device_cus();
   if (cus <= 0 || M == 0) return PartPlan{};
   int32_t Nout[DSV_MAX_GROUP], C[DSV_MAX_GROUP];
-  double steps = 0, longest = 0;
+  double steps = 0, longest = 0, stream = 0;
   for (int i = 0; i < n; ++i) {
     shape(pr[i], &Nout[i], &C[i]);
     const double nk = (C[i] + 63) / 64;
     steps += nk * mtiles * ((Nout[i] + 255) / 256);
     longest = std::max(longest, nk);
+    stream += stream_us(kFullWeightBytesPerUs, M, Nout[i], C[i]);
   }
   // tiles in rounds over the CUs, the longest contraction setting the round
   const double rounds = steps / cus / longest, part = rounds - std::floor(rounds);
-  const double whole = (std::floor(rounds) + (part > 0.5 ? 1.0 : part > 0.0 ? 0.7 : 0.0)) * longest * kTileStepUs;
-  const PartPlan pp = part_plan(pass == 0 ? &p : nullptr, M, n, Nout, C, whole);
+  double whole = (std::floor(rounds) + (part > 0.5 ? 1.0 : 0.0)) * (kTileStep[2] * longest + kTileEnd[2]);
+  if (part > 0.0 && part <= 0.5) whole += kHalfStep * longest + kTileEnd[2];
+  const PartPlan pp = part_plan(pass == 0 ? &p : nullptr, M, n, Nout, C, std::max(whole, stream));
   for (int i = 0; pp.use && i < n; ++i)
     if (!(pass == 0 ? fwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N) : bwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N)).sk_tiles &&
         !(pass == 0 ? fwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N) : bwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N)).use)

@@ -163,7 +163,7 @@ def test_zero_B_is_the_same_base_whatever_the_grouping(T, K, N):
         print("T=%d K=%d N=%d gathered %d: %s" % (T, K, N, plan.counts()["gathered_rows"],
                                                   dsv.gemm_config(plan, dsv.BF16, K, N, 0)), flush=True)
         outs["fwd"].append(dsv.cobatch_fwd(plan, X, W, A, B)[0])
-        outs["noalloc"].append(dsv.cobatch_fwd_noalloc(plan, X, W, A, B)[0])
+        outs["noalloc"].append(dsv.cobatch_fwd_noalloc(plan, X, W, A, B, torch.empty_like(outs["fwd"][0]))[0])
     torch.cuda.synchronize()
     for ys in outs.values():
         assert all(torch.equal(_bits(y), _bits(ys[0])) for y in ys[1:])

@@ -63,6 +63,16 @@ class Recorded:
         pr = b"".join(self.dsv._FWD_PACK(K, N, BUF, BUF, BUF, BUF, BUF, BUF, 0, 0, 0) for K, N in shapes)
         return self.call(self.lib.dsv_cobatch_fwd_grouped, p.handle, 0, len(shapes), pr, WS, n, None)
 
+    def bwd_grouped(self, p, shapes, wt=True, dropout=False, short=0):
+        n = self.dsv.bwd_grouped_workspace_bytes(p, 0, shapes) - short
+        pr = b"".join(self.dsv._BWD_PACK(K, N, BUF, BUF, BUF, BUF, BUF, BUF, BUF, BUF, BUF, BUF if wt else 0,
+                                         0, 0, 0, 0, 0) for K, N in shapes)
+        args = (p.handle, 0, len(shapes), pr, 0)
+        if not dropout:
+            return self.call(self.lib.dsv_lora_bwd_grouped, *args, WS, n, None)
+        drops = (self.dsv.Dropout * len(shapes))(*[self.dsv.Dropout(0.05, 1, i, None) for i in range(len(shapes))])
+        return self.call(self.lib.dsv_lora_bwd_grouped_dropout, *args, drops, WS, n, None)
+
 
 @pytest.fixture(scope="module")
 def rec(tmp_path_factory):
@@ -104,8 +114,8 @@ def test_noalloc_pieces_stay_inside_the_scratch(rec):
     """Pieces of the allocation-free forward lie within the 64 MiB scratch, however the
     rows are grouped, up to the largest that fit."""
     base, most = rec.lib.recorder_scratch(), 0
-    for K, N in ((4096, 4096), (4096, 14336), (14336, 4096), (8192, 28672)):
-        for T in (1, 33, 200, 256, 292, 365, 480, 1300):
+    for K, N in ((4096, 4096), (4096, 14336), (14336, 4096), (28672, 8192), (65536, 8192)):
+        for T in (1, 33, 200, 256, 365, 600, 620, 638, 655, 768):
             for p in (rec.plan([(0, T, 0, 0)], [64], 64), rec.plan([(t, 1, t % 2, 0) for t in range(T)], [64] * 2, 64)):
                 rc, launches = rec.noalloc(p, K, N)
                 for l in launches:
@@ -113,4 +123,31 @@ def test_noalloc_pieces_stay_inside_the_scratch(rec):
                         ends = [l["part"] + l["bytes"] - base, l["h_part"] + l["h_bytes"] - base]
                         assert l["part"] >= base and l["h_part"] >= base and max(ends) <= SCRATCH, (K, N, T, l)
                         most = max(most, *ends)
-    assert most > SCRATCH // 2
+    assert most > SCRATCH * 7 // 8
+
+
+# Calls timed both ways on MI355X (one segment): projections, rows, microseconds in pieces
+# and in tiles.
+TIMED = [
+    # forward, one projection
+    ("fwd", [(64, 131072)], 256, 73.6, 25.2), ("fwd", [(1024, 32768)], 128, 34.2, 23.0),
+    ("fwd", [(512, 14336)], 256, 23.6, 14.4), ("fwd", [(512, 4096)], 200, 17.9, 13.9),
+    ("fwd", [(4096, 131072)], 128, 311.8, 202.4), ("fwd", [(4096, 14336)], 304, 69.0, 58.3),
+    ("fwd", [(5120, 14336)], 380, 109.7, 87.4), ("fwd", [(8192, 28672)], 76, 125.2, 209.9),
+    ("fwd", [(28672, 8192)], 240, 150.1, 179.1), ("fwd", [(4096, 4096)], 360, 30.3, 45.5),
+    # ... two
+    ("fwd", [(8192, 28672)] * 2, 209, 315.5, 248.6), ("fwd", [(5120, 28672)] * 2, 256, 215.6, 144.0),
+    ("fwd", [(4096, 14336)] * 2, 515, 198.5, 155.2), ("fwd", [(4096, 4096)] * 2, 60, 22.8, 60.2),
+    # backward
+    ("bwd", [(14336, 512)], 250, 42.7, 33.9), ("bwd", [(14336, 4096)], 323, 91.2, 71.8),
+    ("bwd", [(28672, 1024)], 248, 57.4, 46.1), ("bwd", [(4096, 14336)], 240, 63.8, 72.2),
+    ("bwd", [(4096, 14336)] * 2, 436, 142.1, 192.4), ("bwd", [(28672, 5120)] * 2, 240, 282.1, 207.1),
+]
+
+
+@pytest.mark.parametrize("what,shapes,T,pieces_us,tiles_us", TIMED)
+def test_the_faster_of_pieces_and_tiles_runs(rec, what, shapes, T, pieces_us, tiles_us):
+    p = rec.plan([(0, T, 0, int(what == "bwd"))], [16], 16)
+    rc, launches = rec.fwd_grouped(p, shapes) if what == "fwd" else rec.bwd_grouped(p, shapes)
+    kinds = {l["kind"] for l in launches if re.match("part|gemm|group", l["kind"])}
+    assert rc == rec.dsv.OK and (kinds == {"part"}) == (pieces_us < tiles_us), (kinds, launches)
