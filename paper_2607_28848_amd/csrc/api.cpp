@@ -114,11 +114,12 @@ GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool al
 //            output at 2.1; in the forward the shrink's read of X at 3.6
 //   pieces   per step and round kPieceStep and kPieceEnd, at least the weights at 5 .. 6
 //            TB/s; 2.5 us per 2^20 fp32 elements of the pieces written and summed, and
-//            kPieceSum more than the tiles for the launch that sums them
-// The forward's pieces must be 4% ahead, above kPartRows rows any pieces 10% (there a
+//            kPieceSum (above 256 rows kPieceSumRows) more than the tiles for the
+//            launch that sums them
+// The forward's pieces must be 4% ahead, above kPartRows rows any pieces 5% more (there a
 // wrong guess costs most).  Of the fitted calls, the choice is the slower by more than
-// 3% and 0.3 us, pieces where tiles were faster, in 0.6% of the single and 0.7% of the
-// grouped forwards' pieces and 7% (2 us of 30, short contractions) and 0.1% of the
+// 3% and 0.3 us, pieces where tiles were faster, in 0.4% of the single and 0.4% of the
+// grouped forwards' pieces and 5% (2 us of 30, short contractions) and 0.1% of the
 // backwards'; at the Llama projections by 12% at most.
 //   K = N = 4096, 8 rows: 12 us in pieces, 38 in tiles; K = 1024, N = 32768, 128 rows:
 //   34 and 23, so tiles; K = 4096, N = 14336, 304 rows: 69 and 58, so tiles
@@ -140,7 +141,7 @@ constexpr double kPartBytesPerUs = 5e6, kWeightBytesPerUs = 5.5e6;
 constexpr double kTileStep[3] = {0.6, 0.98, 1.5}, kTileEnd[3] = {4.4, 5.2, 7.4}, kTileWeightBytesPerUs[3] = {3.7e6, 5.2e6, 3.4e6}, kFullWeightBytesPerUs = 4.2e6;
 constexpr double kHalfStep = 0.81, kSplitSum = 20.0, kSplitBytesPerUs = 13e6, kOutBytesPerUs = 2.1e6, kShrinkBytesPerUs = 3.6e6;
 constexpr double kPieceStep[kPartCfgs] = {0.21, 0.47, 0.56, 0.89}, kPieceEnd[kPartCfgs] = {0.65, 0.55, 1.2, 0.0};
-constexpr double kPieceWeightBytesPerUs[kPartCfgs] = {6.0e6, 5.8e6, 5.0e6, 5.0e6}, kPieceElemUs = 2.5e-6, kPieceSum = 2.7, kFwdMargin = 0.96, kRowsMargin = 0.9;
+constexpr double kPieceWeightBytesPerUs[kPartCfgs] = {6.0e6, 5.8e6, 5.0e6, 5.0e6}, kPieceElemUs = 2.5e-6, kPieceSum = 2.7, kPieceSumRows = 5.2, kFwdMargin = 0.96, kRowsMargin = 0.95;
 
 // Time of a tiles' launch at least: its weights and output.
 double stream_us(double weight_bytes_per_us, int32_t M, int32_t Nout, int32_t C) {
@@ -196,7 +197,7 @@ PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout,
         t_best = us;
         best.cfg = cfg;
         piece_us = std::max(rounds * (kPieceStep[cfg] * t + kPieceEnd[cfg]), w_bytes / kPieceWeightBytesPerUs[cfg]) +
-                   kPieceElemUs * elems + kPieceSum;
+                   kPieceElemUs * elems + (M <= 256 ? kPieceSum : kPieceSumRows);
         for (int i = 0; i < n; ++i) best.split[i] = (nk[i] + t - 1) / t;
       }
     }
