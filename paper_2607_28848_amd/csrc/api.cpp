@@ -1199,11 +1199,16 @@ GemmPlan whole256(int32_t m256, int32_t n_out) {
 // Halves the tiles of a grouped launch's last, partial wave where they fill at
 // most half the CUs (plan_gemm's rule).  Only for projections of one contraction
 // length, whose waves end together; ok: the launch's kernels have half tiles.
-void halve_last_wave(GemmGroup& G, bool ok) {
+// beside_wide: dX beside the dA reduction of ranks above 32 on the side stream.  Halves
+// on nearly every CU leave that work none to run on, which costs more than they gain
+// while the contraction is short (501 rows through two 512 x 8192, rank 64: 128 tiles 69
+// us, 256 halves 82; at 64 K-steps the halves win): seven CUs of eight at most there.
+void halve_last_wave(GemmGroup& G, bool ok, bool beside_wide = false) {
   const int cus = device_cus();
+  const int most = beside_wide && (G.a[0].C + 63) / 64 <= 32 ? cus - cus / 8 : cus;
   for (int p = 1; p < G.n; ++p) ok = ok && (G.a[p].C + 63) / 64 == (G.a[0].C + 63) / 64;
   int32_t r = ok && cus > 0 ? G.off[G.n] % cus : 0;
-  if (2 * r > cus) r = 0;
+  if (2 * r > most) r = 0;
   for (int p = G.n - 1; p >= 0 && r > 0; --p) {
     GemmArgs& g = G.a[p];
     g.half_tiles = std::min(r, g.dp_tiles);
@@ -1726,7 +1731,7 @@ int bwd_grouped_impl(const dsv_plan* p, dsv_dtype dt, int32_t n_proj, const dsv_
       if (G.n > 0) {
         bool ok = true;
         for (int k = 0; k < G.n; ++k) ok = ok && (nt || nn16_fits(G.a[k]));
-        halve_last_wave(G, ok);
+        halve_last_wave(G, ok, p->r_train > 32);
         const int tk = timing_begin(1, s);
         const hipError_t e = nt ? launch_gemm_group_nt(G, s) : launch_gemm_group_nn(G, s);
         timing_end(tk, s);

@@ -151,3 +151,13 @@ def test_the_faster_of_pieces_and_tiles_runs(rec, what, shapes, T, pieces_us, ti
     rc, launches = rec.fwd_grouped(p, shapes) if what == "fwd" else rec.bwd_grouped(p, shapes)
     kinds = {l["kind"] for l in launches if re.match("part|gemm|group", l["kind"])}
     assert rc == rec.dsv.OK and (kinds == {"part"}) == (pieces_us < tiles_us), (kinds, launches)
+
+
+@pytest.mark.parametrize("rank,N,halves", [(64, 512, 0), (64, 4096, 128), (16, 512, 128)])
+def test_halves_leave_room_for_wide_side_work(rec, rank, N, halves):
+    """Grouped backward of 501 rows through two projections of 8192 columns, 128 tiles: over
+    a short contraction they stay whole where the dA reduction of rank 64 runs beside them."""
+    p = rec.plan([(0, 501, 0, 1)], [rank], 64)
+    rc, launches = rec.bwd_grouped(p, [(8192, N)] * 2)
+    tiles = [l for l in launches if l["kind"] == "group_nt"]
+    assert rc == rec.dsv.OK and len(tiles) == 2 and sum(l["half"] for l in tiles) == halves, launches
