@@ -30,10 +30,12 @@ def to_host(t) -> np.ndarray:
 
 
 class Run:
-    """One projection of a workload through the GPU path."""
+    """One projection of a workload through the GPU path.  ws_short: workspaces that many
+    bytes smaller than asked for (bf16: no room for a product in pieces, so tiles run)."""
 
-    def __init__(self, w: wl.Workload, p: int = 0, pad=np.nan, tensors=None):
+    def __init__(self, w: wl.Workload, p: int = 0, pad=np.nan, tensors=None, ws_short: int = 0):
         from paper_2607_28848_amd import dsv
+        self.ws_short = ws_short
         self.w = w
         self.t = tensors if tensors is not None else w.tensors(p, pad=pad)
         self.plan = dsv.segments_build(w.segments, w.n_tokens, w.ranks, w.scales, w.r_max,
@@ -44,13 +46,23 @@ class Run:
         self.dY = to_dev(st["dY"], w.dtype)
         self.dsv = dsv
 
+    def _ws(self, need):
+        import torch
+        return torch.empty(need - self.ws_short, dtype=torch.uint8, device="cuda") if self.ws_short else None
+
+    def fwd_ws(self):
+        return self._ws(self.dsv.fwd_workspace_bytes(self.plan, self.dsv.BF16, self.X.shape[1], self.W.shape[0]))
+
+    def bwd_ws(self):
+        return self._ws(self.dsv.bwd_workspace_bytes(self.plan, self.dsv.BF16, self.X.shape[1], self.W.shape[0]))
+
     def fwd(self, H_save=None):
-        Y, H = self.dsv.cobatch_fwd(self.plan, self.X, self.W, self.A, self.B, H_save=H_save)
+        Y, H = self.dsv.cobatch_fwd(self.plan, self.X, self.W, self.A, self.B, H_save=H_save, workspace=self.fwd_ws())
         return Y, H
 
     def bwd(self, H_save, dA=None, dB=None, accumulate=False, want_dx=True):
         return self.dsv.lora_bwd(self.plan, self.X, self.W, self.A, self.B, H_save, self.dY,
-                                 dA=dA, dB=dB, want_dx=want_dx, accumulate=accumulate)
+                                 dA=dA, dB=dB, want_dx=want_dx, accumulate=accumulate, workspace=self.bwd_ws())
 
 
 def oracle_fwd(w, t, rows=None, drop=None):

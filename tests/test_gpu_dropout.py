@@ -140,19 +140,24 @@ SPLIT = ([(0, 180, 1, 0)] + [(180 + i, 1, 2 + i % 3, 0) for i in range(20)] +
 SPLIT_RANKS = [16, 8, 32, 64, 5]
 
 
-def test_dropout_split_tiles_ragged():
+@pytest.mark.parametrize("wt", [False, True])
+def test_dropout_split_tiles_ragged(wt):
     """Dropout through 256 x 256 tiles split along the contraction (the dX GEMM adds
     the masked low-rank term in the kernel that sums the pieces): T = 700, T_t = 300,
-    K = 4096, N = 2000; Y and dX on sampled rows, H_save, dA and dB in full."""
+    K = 4096, N = 2000, W as it is and transposed; Y and dX on sampled rows, H_save, dA and
+    dB in full.  With all the workspace asked for these calls run in pieces, so it is 256
+    bytes short of them."""
     import torch
-    _say("case dropout split tiles")
+    _say("case dropout split tiles wt=%s" % wt)
     w = wl.custom(SPLIT, SPLIT_RANKS, K=4096, N=2000, r_max=64, name="dropout_split")
-    run = Run(w)
-    bc = run.dsv.gemm_config(run.plan, run.dsv.BF16, 4096, 2000, 1)
-    _say("  dX gemm config %s" % bc)
+    run = Run(w, ws_short=256)
+    cfg = [run.dsv.gemm_config(run.plan, run.dsv.BF16, 4096, 2000, i) for i in range(2)]
+    _say("  gemm configs: fwd %s dX %s" % tuple(cfg))
+    assert all(c["split_tiles"] == 0 or c["tile_m"] < 256 for c in cfg)
     d = (0.05, SEED, OFFSET)
-    Y, H = run.dsv.cobatch_fwd(run.plan, run.X, run.W, run.A, run.B, dropout=d)
-    dA, dB, dX = run.dsv.lora_bwd(run.plan, run.X, run.W, run.A, run.B, H, run.dY, dropout=d)
+    Y, H = run.dsv.cobatch_fwd(run.plan, run.X, run.W, run.A, run.B, dropout=d, workspace=run.fwd_ws())
+    (dA, dB, dX), = run.dsv.lora_bwd_grouped(run.plan, [(run.X, run.W, run.A, run.B, H, run.dY)], dropouts=[d],
+                                             wts=[run.W.t().contiguous()] if wt else None, workspace=run.bwd_ws())
     torch.cuda.synchronize()
     rows = np.unique(np.concatenate([np.arange(0, 700, 7), [179, 180, 199, 200, 499, 500, 699]]))
     dx_rows = np.unique(np.concatenate([np.arange(0, 300, 5), [255, 256, 299]]))

@@ -168,3 +168,91 @@ def test_zero_B_is_the_same_base_whatever_the_grouping(T, K, N):
     for ys in outs.values():
         assert all(torch.equal(_bits(y), _bits(ys[0])) for y in ys[1:])
         assert oracle.rel_err(to_host(ys[0][::37]), to_host(X[::37]) @ to_host(W).T) <= TOL_BF16
+
+
+# T = T_t of groups of two 2056 x 2056 projections, and the tile of their pieces (both passes).
+WIDE_PIECES = {290: (128, 128), 490: (128, 256)}
+
+
+@pytest.mark.parametrize("drop", [False, True])
+@pytest.mark.parametrize("T", sorted(WIDE_PIECES))
+def test_wide_pieces_one_weight_transposed(T, drop):
+    """The pieces' 128 x 128 and 128 x 256 tiles, with ragged rows, columns and contraction
+    (2056 = 8 * 256 + 8 = 32 * 64 + 8), in a group whose backward has the transposed weight of its second
+    projection only: two launches of pieces, NN and NT, and one sum over both.  dX also with
+    both weights as they are and both transposed, against the reference each time."""
+    import torch
+    from paper_2607_28848_amd import dsv
+    K = N = 2056
+    w = wl.custom([(0, 100, 0, 1), (100, 29, 1, 1), (129, T - 129, 2, 1)], [12, 8, 5], K=K, N=N, r_max=12, name="wide")
+    w.projections = [wl.Projection("p%d" % i, K, N) for i in range(2)]
+    ts = [w.tensors(i, pad=np.nan) for i in range(2)]
+    d = [{k: to_dev(t.store[k], "bf16") for k in ("X", "W", "A", "B", "dY")} for t in ts]
+    wt = [x["W"].t().contiguous() for x in d]
+    plan = dsv.segments_build(w.segments, T, w.ranks, w.scales, w.r_max, device="cuda")
+    drops = [(0.1, 5, 1), (0.1, 5, 2)] if drop else None
+    keep = [oracle.dropout_multipliers(T, K, *drops[i]) if drop else None for i in range(2)]
+    w.projections = w.projections[:1]
+    print("T=%d drop=%s" % (T, drop), flush=True)
+    out = dsv.cobatch_fwd_grouped(plan, [(x["X"], x["W"], x["A"], x["B"]) for x in d], dropouts=drops)
+    grads = {}
+    for wts in ((None, wt[1]), (None, None), (wt[0], wt[1])):
+        grads[tuple(x is not None for x in wts)] = dsv.lora_bwd_grouped(
+            plan, [(x["X"], x["W"], x["A"], x["B"], o[1], x["dY"]) for x, o in zip(d, out)], dropouts=drops, wts=list(wts))
+    torch.cuda.synchronize()
+    for i in range(2):
+        errs = {"Y": oracle.rel_err(to_host(out[i][0]), oracle_fwd(w, ts[i], drop=keep[i])[0])}
+        _, dAr, dBr, dXr = oracle_bwd(w, ts[i], drop=keep[i])
+        for which, g in grads.items():
+            errs["dX %s %s" % which] = oracle.rel_err(to_host(g[i][2]), dXr)
+            dA, dB = to_host(g[i][0]), to_host(g[i][1])
+            for a, r in train_mask_slices(w):
+                errs["dA%d %s %s" % ((a,) + which)] = oracle.rel_err(dA[a, :r], dAr[a, :r])
+                errs["dB%d %s %s" % ((a,) + which)] = oracle.rel_err(dB[a, :, :r], dBr[a, :, :r])
+        print("  p%d " % i + ", ".join("%s=%.1e" % kv for kv in errs.items()), flush=True)
+        for k, v in errs.items():
+            assert v <= TOL_BF16, (i, k, v)
+
+
+# T_t, K, N, projections of a masked backward whose dX has half tiles, and the tiles that
+# stay whole and the tiles halved of one launch.
+MASKED_HALVES = [
+    (3073, 1024, 4096, 2, 0, 104),   # the last row tile ends in its first half
+    (3300, 1024, 4096, 2, 0, 104),   # ... in its second
+    (2049, 2048, 2048, 1, 0, 72),    # single calls: halves only ...
+    (5000, 4104, 2048, 1, 256, 84),  # ... and behind whole tiles, the last column tile 8 wide
+]
+
+
+@pytest.mark.parametrize("wt", [False, True])
+@pytest.mark.parametrize("Tt,K,N,n,whole,halves", MASKED_HALVES)
+def test_masked_half_tiles(Tt, K, N, n, whole, halves, wt):
+    """Half tiles that mask the low-rank term (dX under dropout), adapter runs that begin and
+    end inside halves: against the reference at the halves' and tiles' edges, and the same
+    bits as whole tiles (a group of three, whose last wave is too full for halves)."""
+    import torch
+    from paper_2607_28848_amd import dsv
+    segs = [(0, 200, 0, 1), (200, Tt - 300, 1, 1), (Tt - 100, 99, 2, 1), (Tt - 1, 1, 0, 1)]
+    w = wl.custom(segs, [16, 8, 40], K=K, N=N, r_max=64, name="masked_half")
+    t = w.tensors(0, pad=np.nan)
+    d = {k: to_dev(t.store[k], "bf16") for k in ("X", "W", "A", "B", "dY")}
+    plan = dsv.segments_build(w.segments, w.n_tokens, w.ranks, w.scales, w.r_max, device="cuda")
+    drop = (0.1, 5, 1)
+    _, H = dsv.cobatch_fwd(plan, d["X"], d["W"], d["A"], d["B"], dropout=drop)
+    Wt = d["W"].t().contiguous() if wt else None
+    print("T_t=%d K=%d N=%d n=%d wt=%s" % (Tt, K, N, n, wt), flush=True)
+
+    def grads(m):
+        return dsv.lora_bwd_grouped(plan, [(d["X"], d["W"], d["A"], d["B"], H, d["dY"])] * m, dropouts=[drop] * m,
+                                    wts=[Wt] * m if wt else None)
+
+    got = grads(n) + (grads(3) if n > 1 else [])
+    torch.cuda.synchronize()
+    for g in got[1:]:
+        assert torch.equal(_bits(g[2]), _bits(got[0][2]))
+    rows = np.unique(np.concatenate([np.arange(0, Tt, 307), [127, 128, 199, 200, 255, 256, 383, 384, Tt - 101, Tt - 100,
+                                                             (Tt - 1) // 256 * 256, Tt - 2, Tt - 1]])).astype(np.int32)
+    dXr = oracle_bwd(w, t, dx_rows=rows, drop=oracle.dropout_multipliers(Tt, K, *drop))[3]
+    err = oracle.rel_err(to_host(got[0][2])[rows], dXr)
+    print("  dX %.2e" % err, flush=True)
+    assert err <= TOL_BF16

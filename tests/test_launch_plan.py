@@ -51,8 +51,8 @@ class Recorded:
             out.append(dict({"kind": kind}, **{k: int(v) for k, v in (x.split("=") for x in kv)}))
         return rc, out
 
-    def fwd(self, p, K, N, dtype=0):
-        n = self.dsv.fwd_workspace_bytes(p, dtype, K, N)
+    def fwd(self, p, K, N, dtype=0, short=0):
+        n = self.dsv.fwd_workspace_bytes(p, dtype, K, N) - short
         return self.call(self.lib.dsv_cobatch_fwd, p.handle, dtype, K, N, BUF, BUF, BUF, BUF, BUF, BUF, WS, n, None)
 
     def noalloc(self, p, K, N):
@@ -161,3 +161,54 @@ def test_halves_leave_room_for_wide_side_work(rec, rank, N, halves):
     rc, launches = rec.bwd_grouped(p, [(8192, N)] * 2)
     tiles = [l for l in launches if l["kind"] == "group_nt"]
     assert rc == rec.dsv.OK and len(tiles) == 2 and sum(l["half"] for l in tiles) == halves, launches
+
+
+# What the GPU tests below are named for, at 256 compute units.
+
+def test_gpu_tests_of_split_tiles_reach_them(rec):
+    """A workspace 256 bytes short of the pieces: 256 x 256 tiles split along the contraction."""
+    import test_gpu_dropout
+    import test_gpu_parity
+    for m in (test_gpu_parity, test_gpu_dropout):
+        p = rec.plan(m.SPLIT, m.SPLIT_RANKS, 64)
+        calls = [rec.fwd(p, 4096, 2000, short=256), rec.bwd_grouped(p, [(4096, 2000)], wt=False, short=256)]
+        calls += [rec.bwd_grouped(p, [(4096, 2000)], wt=wt, dropout=True, short=256) for wt in (False, True)]
+        for i, (rc, launches) in enumerate(calls):
+            l, = [l for l in launches if re.match("part|gemm|group", l["kind"])]
+            assert rc == rec.dsv.OK and l["tm"] == 256 and l["split"] == l["tiles"] > 0 and l["pieces"] > 1
+            assert l["drop"] == (i >= 2) and l["kind"] == ("gemm_nt" if i in (0, 3) else "gemm_nn")
+
+
+def test_gpu_tests_of_half_tiles_reach_them(rec):
+    """Masked dX: the whole and the halved tiles, with W as it is and transposed; the group of
+    three that the bits are compared with has whole tiles only."""
+    import test_gpu_pieces
+    for Tt, K, N, n, whole, halves in test_gpu_pieces.MASKED_HALVES:
+        p = rec.plan([(0, 200, 0, 1), (200, Tt - 300, 1, 1), (Tt - 100, 99, 2, 1), (Tt - 1, 1, 0, 1)], [16, 8, 40], 64)
+        for wt in (False, True):
+            for m, want in ((n, (whole, halves)), (3, (None, 0))):
+                if m != n and n == 1:
+                    continue
+                rc, launches = rec.bwd_grouped(p, [(K, N)] * m, wt=wt, dropout=True)
+                tiles = [l for l in launches if re.match("part|gemm|group", l["kind"])]
+                assert rc == rec.dsv.OK and all(l["drop"] and l["split"] == 0 for l in tiles)
+                assert sum(l["half"] for l in tiles) == want[1], (Tt, m, tiles)
+                assert want[0] is None or sum(l["whole"] for l in tiles) == want[0], (Tt, m, tiles)
+
+
+def test_gpu_tests_of_pieces_reach_every_tile(rec):
+    """The pieces' four tiles in each pass."""
+    import test_gpu_pieces as tp
+    seen = {"fwd": set(), "bwd": set()}
+    for T, Tt, K, N, r_max, ranks in tp.CASES:
+        p = rec.plan(tp._segments(T, Tt, len(ranks)), ranks, r_max)
+        for shapes in ([(K, N)], [(K, N), (K, 2 * N)]):
+            seen["fwd"] |= {l["cfg"] for l in rec.fwd_grouped(p, shapes)[1] if l["kind"] == "part"}
+            seen["bwd"] |= {l["cfg"] for l in rec.bwd_grouped(p, shapes)[1] if l["kind"] == "part"} if Tt else set()
+    for T, tile in tp.WIDE_PIECES.items():
+        p = rec.plan([(0, 100, 0, 1), (100, 29, 1, 1), (129, T - 129, 2, 1)], [12, 8, 5], 12)
+        for ps, call in (("fwd", rec.fwd_grouped), ("bwd", rec.bwd_grouped)):
+            cfg, = {l["cfg"] for l in call(p, [(2056, 2056)] * 2)[1] if l["kind"] == "part"}
+            assert cfg == {(128, 128): 2, (128, 256): 3}[tile]
+            seen[ps].add(cfg)
+    assert seen == {"fwd": {0, 1, 2, 3}, "bwd": {0, 1, 2, 3}}
