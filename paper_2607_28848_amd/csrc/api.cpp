@@ -123,6 +123,12 @@ GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool al
 // backwards'; at the Llama projections by 12% at most.
 //   K = N = 4096, 8 rows: 12 us in pieces, 38 in tiles; K = 1024, N = 32768, 128 rows:
 //   34 and 23, so tiles; K = 4096, N = 14336, 304 rows: 69 and 58, so tiles
+// Narrow outputs take pieces at thousands of rows too (K = 2048, N = 64, 16384 training rows:
+// dX 54 us, tiles 73).  There the shrink fills CUs that the pieces want: above 2048 rows a
+// growing part of its read of X is added to them, from 8192 all of it (K = 8192, N = 512, 8192
+// rows: 114 us, tiles 102), and no forward beyond takes them (K = 4096, N = 256, 32768 rows: 160
+// and 135; three K = 4096, N = 64, 16384 rows: 218 and 178); nor dX above the 32768 rows timed,
+// which keeps the sum's grid of rows within 65535 however many adapters they have.
 // A forward's choice depends on the number of rows and the shapes, never on how the
 // rows are grouped into segments (the launch that gathered rows cost the tiles, about
 // 6 us, is left out for that): the base product of a row is the same bits in every
@@ -135,7 +141,7 @@ struct PartPlan {
   size_t h_off[kMaxGroup] = {};           // forward: the shrink's pieces
   size_t bytes_any = 0;                   // forward: the most `bytes` of any grouping of the rows
 };
-constexpr int kMinPartSteps = 4, kPartRows = 1024;
+constexpr int kMinPartSteps = 4, kPartRows = 1024, kFwdPartRows = 8192, kBwdPartRows = 32768;
 constexpr double kPartBytesPerUs = 5e6, kWeightBytesPerUs = 5.5e6;
 // 128 x 128 tiles with one workgroup per CU, with two, 256 x 256 tiles
 constexpr double kTileStep[3] = {0.6, 0.98, 1.5}, kTileEnd[3] = {4.4, 5.2, 7.4}, kTileWeightBytesPerUs[3] = {3.7e6, 5.2e6, 3.4e6}, kFullWeightBytesPerUs = 4.2e6;
@@ -164,7 +170,7 @@ double tiles_us(const GemmPlan& g, int32_t M, int32_t Nout, int32_t C) {
 PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout, const int32_t* C, double t_tiles) {
   PartPlan best;
   const int cus = device_cus();
-  if (cus <= 0 || M <= 0) return best;
+  if (cus <= 0 || M <= 0 || M > (p ? kFwdPartRows : kBwdPartRows)) return best;
   static const int kSplits[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
   double w_bytes = 0, x_bytes = 0, w_us, piece_us = 0, t_best = HUGE_VAL;
   int32_t nk[kMaxGroup], nk_max = 1;
@@ -203,6 +209,7 @@ PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout,
     }
   }
   if (M > kPartRows) t_tiles *= kRowsMargin;
+  if (p) piece_us += std::min(1.0, std::max(0.0, (M - 2048) / 6144.0)) * x_bytes / kShrinkBytesPerUs;
   best.use = piece_us > 0 && piece_us < (p ? kFwdMargin * (t_tiles + x_bytes / kShrinkBytesPerUs) : t_tiles);
   if (best.use)
     for (int i = 0; i < n; ++i) {

@@ -595,6 +595,7 @@ hipError_t launch_part_gemm(const PartGroup& g, int cfg, int32_t r_sel, bool nn,
 hipError_t launch_part_finish(FinishGroup g, int32_t n_items, int32_t r_sel, bool bwd, hipStream_t s) {
   if (g.n <= 0 || g.n > kMaxGroup || n_items <= 0 || r_sel < 1 || r_sel > 64) return hipErrorInvalidValue;
   const int64_t xs = bwd ? n_items : 2 * (int64_t)n_items;
+  if (xs > 65535) return hipErrorInvalidValue;
   int64_t blocks = 0;
   for (int p = 0; p < g.n; ++p) blocks += (g.a[p].Nout + 255) / 256;
   // Several blocks per workgroup once single ones would give every CU four

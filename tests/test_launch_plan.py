@@ -135,10 +135,14 @@ TIMED = [
     ("fwd", [(4096, 131072)], 128, 311.8, 202.4), ("fwd", [(4096, 14336)], 304, 69.0, 58.3),
     ("fwd", [(5120, 14336)], 380, 109.7, 87.4), ("fwd", [(8192, 28672)], 76, 125.2, 209.9),
     ("fwd", [(28672, 8192)], 240, 150.1, 179.1), ("fwd", [(4096, 4096)], 360, 30.3, 45.5),
-    # ... two
-    ("fwd", [(8192, 28672)] * 2, 209, 315.5, 248.6), ("fwd", [(5120, 28672)] * 2, 256, 215.6, 144.0),
+    ("fwd", [(8192, 512)], 8192, 114.2, 101.5), ("fwd", [(14336, 512)], 6144, 140.4, 120.8),
+    ("fwd", [(4096, 512)], 16384, 113.8, 98.5), ("fwd", [(4096, 256)], 32768, 160.3, 134.7),
+    ("fwd", [(4096, 256)], 2500, 29.0, 43.5),
+    # ... two and three
+    ("fwd", [(4096, 64)] * 3, 16384, 217.7, 178.0), ("fwd", [(8192, 28672)] * 2, 209, 315.5, 248.6), ("fwd", [(5120, 28672)] * 2, 256, 215.6, 144.0),
     ("fwd", [(4096, 14336)] * 2, 515, 198.5, 155.2), ("fwd", [(4096, 4096)] * 2, 60, 22.8, 60.2),
     # backward
+    ("bwd", [(64, 2048)], 16384, 54.0, 73.1),
     ("bwd", [(14336, 512)], 250, 42.7, 33.9), ("bwd", [(14336, 4096)], 323, 91.2, 71.8),
     ("bwd", [(28672, 1024)], 248, 57.4, 46.1), ("bwd", [(4096, 14336)], 240, 63.8, 72.2),
     ("bwd", [(4096, 14336)] * 2, 436, 142.1, 192.4), ("bwd", [(28672, 5120)] * 2, 240, 282.1, 207.1),
@@ -151,6 +155,18 @@ def test_the_faster_of_pieces_and_tiles_runs(rec, what, shapes, T, pieces_us, ti
     rc, launches = rec.fwd_grouped(p, shapes) if what == "fwd" else rec.bwd_grouped(p, shapes)
     kinds = {l["kind"] for l in launches if re.match("part|gemm|group", l["kind"])}
     assert rc == rec.dsv.OK and (kinds == {"part"}) == (pieces_us < tiles_us), (kinds, launches)
+
+
+@pytest.mark.parametrize("T", [8192, 8193, 32768, 32769, 70000])
+def test_rows_of_the_sum_fit_its_grid(rec, T):
+    """Every row with an adapter of its own: the sum has a row of workgroups for each 16 rows of
+    an item, at most 65535; more rows than that take tiles."""
+    p = rec.plan([(t, 1, t, 1) for t in range(T)], [4] * T, 4)
+    for K, N in ((8192, 8), (8192, 64), (64, 8192), (8, 8192), (65536, 64), (64, 65536)):
+        for bwd, (rc, launches) in enumerate((rec.fwd(p, K, N), rec.bwd_grouped(p, [(K, N)]))):
+            sums = [l for l in launches if l["kind"] == "finish"]
+            assert rc == rec.dsv.OK and (not sums or (2 - bwd) * sums[0]["items"] <= 65535), (K, N, launches)
+            assert T <= (32768 if bwd else 8192) or not sums, (K, N, launches)
 
 
 @pytest.mark.parametrize("rank,N,halves", [(64, 512, 0), (64, 4096, 128), (16, 512, 128)])
