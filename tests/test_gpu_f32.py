@@ -21,6 +21,10 @@ CASES = [
     ([(0, 32, 0, 0), (32, 33, 1, 1)], [8, 16], 16, 64, 32, 0.0),
     ([(0, 31, 0, 0), (31, 1, 1, 0), (32, 65, 1, 1), (97, 3, 2, 1)], [8, 33, 5], 33, 72, 40, 0.1),
     ([(0, 300, 1, 1), (300, 40, 0, 0), (340, 64, 2, 1), (404, 90, 1, 1)], [16, 64, 30], 64, 520, 136, 0.0),
+    # steps of a token sum packed from many short runs, from part of a long one, and from more than 64
+    ([(i, 1, i % 2, 1) for i in range(150)] + [(150, 70, 0, 1), (220, 3, 1, 1), (223, 300, 0, 1), (523, 5, 1, 1),
+                                               (528, 61, 0, 1)], [33, 5], 33, 72, 40, 0.1),
+    ([(3 * i, 3, i % 3, 1) for i in range(70)], [16, 8, 3], 16, 64, 32, 0.0),
     ([(0, 20, 3, 0), (20, 129, 0, 1), (149, 1, 1, 0)], [32, 7, 8, 10], 34, 1032, 264, 0.3),
 ]
 
