@@ -47,7 +47,11 @@ int device_cus() {
 //     bits as whole tiles; 6144 x 4096 x 4096, 1.5 waves: 160 us, against 182 with
 //     the tiles split in two).  Among the 256 x 256 forms only: the masked
 //     low-rank term of the 128 x 128 form keeps a NaN in its own column, that of
-//     the 256 x 256 form does not.
+//     the 256 x 256 form does not.  Not a forward whose only wave is split in two:
+//     about 120 to 146 K-steps by the costs above, over which the split form gains more
+//     per K-step than its sum costs (1007 x 9016 x 5880: 131 us, 161 in halves; 69
+//     such calls: halves 9% longer on average).  dX keeps halves there: W as it is
+//     gains 6% by them (W transposed loses 9%, and both must give the same bits).
 // The constants were fitted to timings of the Llama-3-8B projections
 // (forward and dX) on MI355X.
 struct GemmPlan {
@@ -60,7 +64,7 @@ constexpr double kEff256 = 1.12;
 constexpr double kSplitCost64 = 0.4;
 constexpr double kHalfTile = 0.55;
 
-GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool allow_split = true) {
+GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool fwd, bool allow_split = true) {
   GemmPlan best;
   best.n_mtiles = m128;
   best.n_ntiles = (n_out + 127) / 128;
@@ -92,7 +96,8 @@ GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool al
     }
   }
   if (cost256 >= cost128) return best;
-  if (r > 0 && 2 * r <= cus && ((double)full + kHalfTile) * 4.0 / kEff256 < cost256) {
+  const bool only_split = fwd && full == 0 && p.sk_split == 2;
+  if (r > 0 && 2 * r <= cus && !only_split && ((double)full + kHalfTile) * 4.0 / kEff256 < cost256) {
     p.dp_tiles = (int32_t)(full * cus);
     p.half_tiles = (int32_t)r;
     p.sk_tiles = p.sk_split = 0;
@@ -299,11 +304,11 @@ BwdWs bwd_ws(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N, const GemmPl
 
 GemmPlan fwd_gemm_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N, bool allow_split = true) {
   if (dt != DSV_BF16 || p.T == 0) return GemmPlan{};
-  return plan_gemm(p.n_ftiles, p.n_ftiles128, N, K, allow_split);
+  return plan_gemm(p.n_ftiles, p.n_ftiles128, N, K, true, allow_split);
 }
 GemmPlan bwd_gemm_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
   if (dt != DSV_BF16 || p.T_t == 0) return GemmPlan{};
-  return plan_gemm(p.n_btiles, p.n_btiles128, K, N);
+  return plan_gemm(p.n_btiles, p.n_btiles128, K, N, false);
 }
 
 // Pieces or tiles of one projection's forward / dX GEMM.

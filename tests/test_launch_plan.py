@@ -157,6 +157,15 @@ def test_the_faster_of_pieces_and_tiles_runs(rec, what, shapes, T, pieces_us, ti
     assert rc == rec.dsv.OK and (kinds == {"part"}) == (pieces_us < tiles_us), (kinds, launches)
 
 
+@pytest.mark.parametrize("T,K,N", [(1007, 9016, 5880), (3908, 8760, 1776), (8128, 8552, 1008)])
+def test_one_wave_over_a_long_contraction_is_split(rec, T, K, N):
+    """Forwards timed in 131, 140 and 155 us with their one partial wave split in two, in 161, 169
+    and 172 with halves."""
+    (rc, launches) = rec.fwd(rec.plan([(0, T, 0, 0)], [16], 16), K, N)
+    l, = [l for l in launches if re.match("part|gemm", l["kind"])]
+    assert rc == rec.dsv.OK and l["kind"] == "gemm_nt" and (l["split"], l["pieces"], l["half"]) == (l["tiles"], 2, 0)
+
+
 @pytest.mark.parametrize("T", [8192, 8193, 32768, 32769, 70000])
 def test_rows_of_the_sum_fit_its_grid(rec, T):
     """Every row with an adapter of its own: the sum has a row of workgroups for each 16 rows of
