@@ -109,31 +109,32 @@ GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool fw
 // above.  Of the pieces' forms the one with the smallest cost is taken: rounds of
 // workgroups over the CUs times K-steps per piece times the configuration's time per
 // step (at least the weights at 5.5 TB/s), plus the fp32 pieces written and read once
-// each at 5 TB/s.  Then its whole time is estimated beside that of the tiles, and the
-// smaller one wins.  Both estimates were fitted to about 20000 calls timed both ways
-// on MI355X, single and groups of two and three, forward and backward, 1 .. 2400 rows,
-// K and N from 64 to 16384 and 131072, one segment:
-//   tiles    (kTileStep us per K-step + kTileEnd) per round of the form, the second
-//            number for a half tile, a split round and its sum: kSplitSum and the fp32
-//            pieces at 13 TB/s more; at least the weights at 3.4 .. 5.2 TB/s and the
-//            output at 2.1; in the forward the shrink's read of X at 3.6
-//   pieces   per step and round kPieceStep and kPieceEnd, at least the weights at 5 .. 6
-//            TB/s; 2.5 us per 2^20 fp32 elements of the pieces written and summed, and
-//            kPieceSum (above 256 rows kPieceSumRows) more than the tiles for the
-//            launch that sums them
-// The forward's pieces must be 4% ahead, above kPartRows rows any pieces 5% more (there a
-// wrong guess costs most).  Of the fitted calls, the choice is the slower by more than
-// 3% and 0.3 us, pieces where tiles were faster, in 0.4% of the single and 0.4% of the
-// grouped forwards' pieces and 5% (2 us of 30, short contractions) and 0.1% of the
-// backwards'; at the Llama projections by 12% at most.
-//   K = N = 4096, 8 rows: 12 us in pieces, 38 in tiles; K = 1024, N = 32768, 128 rows:
-//   34 and 23, so tiles; K = 4096, N = 14336, 304 rows: 69 and 58, so tiles
+// each at 5 TB/s.  Then the pieces are estimated beside the tiles, in microseconds, and
+// the smaller one wins.  The constants below were fitted, by the time that wrong choices
+// cost either way, to 5902 calls timed both ways on MI355X: single, groups of two and three,
+// forward and dX, masked and not, 1 .. 8192 rows, 8 .. 28672 columns, Llama shapes, random
+// ones, and tables of decode, prefill and training segments:
+//   tiles    kTileStep per K-step and kTileEnd per round of the form (kHalfStep, kHalfEnd
+//            for half tiles; a split round and its sum: kSplitSum and the fp32 pieces at
+//            5 TB/s more), at least the stream of the weights
+//   pieces   kPieceStep per K-step of a piece and kPieceEnd per round, at least the stream
+//            of the weights; kPieceElemUs per fp32 element of the pieces; kPieceBase
+// Of the calls, those of Llama shapes and serving tables lose 0.3% (single) and 0.3 .. 2.7%
+// (grouped) to the best choice of each, the random ones 1% and 2.5 .. 8% (groups of unequal
+// projections, whose pieces need that every single call takes pieces or splits its tiles).
+//   K = N = 4096, 8 rows: 12 us in pieces, 38 in tiles; two K = 4096, N = 14336, 90 rows: 62
+//   and 100; K = 1024, N = 32768, 128 rows: 34 and 23, so tiles
+//   kTieUs: a small single call may lose that much by its pieces, so that its group has them
+//   kRowsMargin: above 512 rows a forward's pieces must be that much ahead
+//   kMaskedShrinkUs: a masked forward's shrink is a launch of its own
+//   kSideUs: above 2048 rows tiles hide the grouped backward's dA reduction (two K = 1024, N =
+//   3072, 3399 rows: 84 us, in pieces 100)
 // Narrow outputs take pieces at thousands of rows too (K = 2048, N = 64, 16384 training rows:
-// dX 54 us, tiles 73).  There the shrink fills CUs that the pieces want: above 2048 rows a
-// growing part of its read of X is added to them, from 8192 all of it (K = 8192, N = 512, 8192
-// rows: 114 us, tiles 102), and no forward beyond takes them (K = 4096, N = 256, 32768 rows: 160
-// and 135; three K = 4096, N = 64, 16384 rows: 218 and 178); nor dX above the 32768 rows timed,
-// which keeps the sum's grid of rows within 65535 however many adapters they have.
+// dX 54 us, tiles 73).  There the forward's shrink fills CUs that the pieces want: above 2048
+// rows a growing part of its read of X is added to them, from 8192 all of it (K = 8192, N =
+// 512, 8192 rows: 114 us, tiles 102), and no forward beyond takes them (K = 4096, N = 256, 32768
+// rows: 160 and 135; three K = 4096, N = 64, 16384 rows: 218 and 178); nor dX above the 32768
+// rows timed, which keeps the sum's grid of rows within 65535 however many adapters they have.
 // A forward's choice depends on the number of rows and the shapes, never on how the
 // rows are grouped into segments (the launch that gathered rows cost the tiles, about
 // 6 us, is left out for that): the base product of a row is the same bits in every
@@ -146,33 +147,37 @@ struct PartPlan {
   size_t h_off[kMaxGroup] = {};           // forward: the shrink's pieces
   size_t bytes_any = 0;                   // forward: the most `bytes` of any grouping of the rows
 };
-constexpr int kMinPartSteps = 4, kPartRows = 1024, kFwdPartRows = 8192, kBwdPartRows = 32768;
+constexpr int kMinPartSteps = 4, kFwdPartRows = 8192, kBwdPartRows = 32768;
 constexpr double kPartBytesPerUs = 5e6, kWeightBytesPerUs = 5.5e6;
 // 128 x 128 tiles with one workgroup per CU, with two, 256 x 256 tiles
-constexpr double kTileStep[3] = {0.6, 0.98, 1.5}, kTileEnd[3] = {4.4, 5.2, 7.4}, kTileWeightBytesPerUs[3] = {3.7e6, 5.2e6, 3.4e6}, kFullWeightBytesPerUs = 4.2e6;
-constexpr double kHalfStep = 0.81, kSplitSum = 20.0, kSplitBytesPerUs = 13e6, kOutBytesPerUs = 2.1e6, kShrinkBytesPerUs = 3.6e6;
-constexpr double kPieceStep[kPartCfgs] = {0.21, 0.47, 0.56, 0.89}, kPieceEnd[kPartCfgs] = {0.65, 0.55, 1.2, 0.0};
-constexpr double kPieceWeightBytesPerUs[kPartCfgs] = {6.0e6, 5.8e6, 5.0e6, 5.0e6}, kPieceElemUs = 2.5e-6, kPieceSum = 2.7, kPieceSumRows = 5.2, kFwdMargin = 0.96, kRowsMargin = 0.95;
+constexpr double kTileStep[3] = {0.68, 0.76, 1.37}, kTileEnd[3] = {0.27, 4.53, 5.72}, kTileWeightBytesPerUs[3] = {3.47e6, 5.2e6, 5.05e6};
+constexpr double kOneTileBytesPerUs = 0.129e6, kHalfStep = 1.08, kHalfStepRows128 = 1.18, kHalfEnd = 5.23, kSplitSum = 11.2, kSplitBytesPerUs = 5.02e6;
+constexpr double kPieceStep[kPartCfgs] = {0.21, 0.47, 0.56, 0.89}, kPieceEnd[kPartCfgs] = {0.01, 0.63, 1.54, 0.42};
+constexpr double kPieceWeightBytesPerUs[kPartCfgs] = {6.63e6, 6.5e6, 6.59e6, 4.69e6}, kPieceElemUs = 1.87e-6;
+// what the pieces' other launches cost more than the tiles': up to 256 rows, above; forward, dX; single, grouped
+constexpr double kPieceBase[2][2][2] = {{{-1.9, -9.5}, {1.3, -10.8}}, {{-2.3, 0.7}, {-0.5, -8.7}}};
+constexpr double kMaskedShrinkUs = 5.84, kShrinkBytesPerUs = 7.16e6, kSideUs = 15.0, kTieUs[2] = {1.5, 5.0}, kRowsMargin = 1.1;
 
-// Time of a tiles' launch at least: its weights and output.
-double stream_us(double weight_bytes_per_us, int32_t M, int32_t Nout, int32_t C) {
-  return 2.0 * Nout * C / weight_bytes_per_us + 2.0 * M * Nout / kOutBytesPerUs;
+// Time of 256 x 256 tiles at least: the stream of their weights.
+double stream256_us(double weight_bytes, double tiles) {
+  return weight_bytes / std::min(kTileWeightBytesPerUs[2], kOneTileBytesPerUs * tiles);
 }
+double half_us(int32_t M, double nk) { return (M <= 128 ? kHalfStepRows128 : kHalfStep) * nk + kHalfEnd; }
 double tiles_us(const GemmPlan& g, int32_t M, int32_t Nout, int32_t C) {
   const int64_t cus = device_cus(), nk = (C + 63) / 64;
   if (cus <= 0) return 0.0;  // no device: no launch plan either
   const int form = g.tm == 256 ? 2 : g.dp_tiles <= cus ? 0 : 1;
   const int64_t per = form == 1 ? 2 * cus : cus;
   double t = (double)((g.dp_tiles + per - 1) / per) * (kTileStep[form] * nk + kTileEnd[form]);
-  if (g.half_tiles > 0) t += kHalfStep * nk + kTileEnd[2];
+  if (g.half_tiles > 0) t += half_us(M, nk);
   if (g.sk_tiles > 0)
     t += kTileStep[2] * nk / g.sk_split + kSplitSum + (double)g.sk_tiles * g.sk_split * g.tm * g.tn * 8 / kSplitBytesPerUs;
-  const bool full = form == 2 && g.dp_tiles >= cus;  // tiles on every CU draw more
-  return std::max(t, stream_us(full ? kFullWeightBytesPerUs : kTileWeightBytesPerUs[form], M, Nout, C));
+  const double w_bytes = 2.0 * Nout * C;
+  return std::max(t, form == 2 ? stream256_us(w_bytes, (double)g.n_mtiles * g.n_ntiles) : w_bytes / kTileWeightBytesPerUs[form]);
 }
 
 // p (forward): the plan whose shrink runs beside the pieces.
-PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout, const int32_t* C, double t_tiles) {
+PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout, const int32_t* C, double t_tiles, bool masked) {
   PartPlan best;
   const int cus = device_cus();
   if (cus <= 0 || M <= 0 || M > (p ? kFwdPartRows : kBwdPartRows)) return best;
@@ -207,15 +212,23 @@ PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout,
       if (us < t_best) {
         t_best = us;
         best.cfg = cfg;
-        piece_us = std::max(rounds * (kPieceStep[cfg] * t + kPieceEnd[cfg]), w_bytes / kPieceWeightBytesPerUs[cfg]) +
-                   kPieceElemUs * elems + (M <= 256 ? kPieceSum : kPieceSumRows);
-        for (int i = 0; i < n; ++i) best.split[i] = (nk[i] + t - 1) / t;
+        int32_t steps = 0;
+        for (int i = 0; i < n; ++i) {
+          best.split[i] = (nk[i] + t - 1) / t;
+          steps = std::max(steps, (nk[i] + best.split[i] - 1) / best.split[i]);
+        }
+        piece_us = std::max(rounds * (kPieceStep[cfg] * steps + kPieceEnd[cfg]), w_bytes / kPieceWeightBytesPerUs[cfg]) +
+                   kPieceElemUs * elems;
       }
     }
   }
-  if (M > kPartRows) t_tiles *= kRowsMargin;
+  if (t_best == HUGE_VAL) return best;
+  piece_us += kPieceBase[M > 256][p == nullptr][n > 1];
   if (p) piece_us += std::min(1.0, std::max(0.0, (M - 2048) / 6144.0)) * x_bytes / kShrinkBytesPerUs;
-  best.use = piece_us > 0 && piece_us < (p ? kFwdMargin * (t_tiles + x_bytes / kShrinkBytesPerUs) : t_tiles);
+  if (masked) piece_us += kMaskedShrinkUs;
+  if (p && M > 512) piece_us *= kRowsMargin;
+  if (!p && n > 1 && M > 2048) piece_us += kSideUs;
+  best.use = piece_us < t_tiles + (n == 1 && M <= 256 ? kTieUs[p == nullptr] : 0.0);
   if (best.use)
     for (int i = 0; i < n; ++i) {
       best.n_m[i] = (M + kPartCfg[best.cfg].tm - 1) / kPartCfg[best.cfg].tm;
@@ -312,49 +325,59 @@ GemmPlan bwd_gemm_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
 }
 
 // Pieces or tiles of one projection's forward / dX GEMM.
-PartPlan fwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N, bool allow_split = true) {
+PartPlan fwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N, bool allow_split = true, bool masked = false) {
   if (dt != DSV_BF16 || p.T == 0) return PartPlan{};
-  return part_plan(&p, p.T, 1, &N, &K, tiles_us(fwd_gemm_plan(p, dt, K, N, allow_split), p.T, N, K));
+  return part_plan(&p, p.T, 1, &N, &K, tiles_us(fwd_gemm_plan(p, dt, K, N, allow_split), p.T, N, K), masked);
 }
 PartPlan bwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
   if (dt != DSV_BF16 || p.T_t == 0) return PartPlan{};
-  return part_plan(nullptr, p.T_t, 1, &K, &N, tiles_us(bwd_gemm_plan(p, dt, K, N), p.T_t, K, N));
+  return part_plan(nullptr, p.T_t, 1, &K, &N, tiles_us(bwd_gemm_plan(p, dt, K, N), p.T_t, K, N), false);
 }
 // ... of a grouped call, whose tiles share one launch of whole 256 x 256 tiles.
 // A projection whose single call splits no contraction keeps its whole tiles
 // (its grouped result is the single call's, bit for bit).
 template <typename Proj, typename ShapeOf>
-PartPlan group_part_plan(const dsv_plan& p, int pass, int32_t n, const Proj* pr, ShapeOf shape) {
+PartPlan group_part_plan(const dsv_plan& p, int pass, int32_t n, const Proj* pr, bool masked, ShapeOf shape) {
   const int32_t M = pass == 0 ? p.T : p.T_t, mtiles = pass == 0 ? p.n_ftiles : p.n_btiles;
   const int cus = device_cus();
   if (cus <= 0 || M == 0) return PartPlan{};
   int32_t Nout[DSV_MAX_GROUP], C[DSV_MAX_GROUP];
-  double steps = 0, longest = 0, stream = 0;
+  double tiles = 0, steps = 0, longest = 0, shortest = HUGE_VAL, long_tiles = 0, w_bytes = 0;
   for (int i = 0; i < n; ++i) {
     shape(pr[i], &Nout[i], &C[i]);
-    const double nk = (C[i] + 63) / 64;
-    steps += nk * mtiles * ((Nout[i] + 255) / 256);
-    longest = std::max(longest, nk);
-    stream += stream_us(kFullWeightBytesPerUs, M, Nout[i], C[i]);
+    const double nk = (C[i] + 63) / 64, t = (double)mtiles * ((Nout[i] + 255) / 256);
+    if (nk > longest) longest = nk, long_tiles = 0;
+    if (nk == longest) long_tiles += t;
+    shortest = std::min(shortest, nk);
+    tiles += t / cus;
+    steps += nk * t / cus;
+    w_bytes += 2.0 * Nout[i] * C[i];
   }
-  // tiles in rounds over the CUs, the longest contraction setting the round
-  const double rounds = steps / cus / longest, part = rounds - std::floor(rounds);
-  double whole = (std::floor(rounds) + (part > 0.5 ? 1.0 : 0.0)) * (kTileStep[2] * longest + kTileEnd[2]);
-  if (part > 0.0 && part <= 0.5) whole += kHalfStep * longest + kTileEnd[2];
-  const PartPlan pp = part_plan(pass == 0 ? &p : nullptr, M, n, Nout, C, std::max(whole, stream));
+  auto round = [](double nk) { return kTileStep[2] * nk + kTileEnd[2]; };
+  double whole;
+  if (shortest == longest) {  // rounds over the CUs, the last one of halves where they fit
+    const double part = tiles - std::floor(tiles);
+    whole = (std::floor(tiles) + (part > 0.5 ? 1.0 : 0.0)) * round(longest);
+    if (part > 0.0 && part <= 0.5) whole += half_us(M, longest);
+  } else {  // the shorter ones fill up behind the longest
+    whole = std::max(std::ceil(long_tiles / cus) * round(longest),
+                     kTileStep[2] * (steps + 0.5 * shortest) + kTileEnd[2] * (tiles + 0.5));
+  }
+  whole = std::max(whole, stream256_us(w_bytes, tiles * cus));
+  const PartPlan pp = part_plan(pass == 0 ? &p : nullptr, M, n, Nout, C, whole, masked);
   for (int i = 0; pp.use && i < n; ++i)
     if (!(pass == 0 ? fwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N) : bwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N)).sk_tiles &&
-        !(pass == 0 ? fwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N) : bwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N)).use)
+        !(pass == 0 ? fwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N, true, masked) : bwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N)).use)
       return PartPlan{};
   return pp;
 }
-PartPlan fwd_group_part(const dsv_plan& p, dsv_dtype dt, int32_t n, const dsv_fwd_proj* pr) {
+PartPlan fwd_group_part(const dsv_plan& p, dsv_dtype dt, int32_t n, const dsv_fwd_proj* pr, bool masked = false) {
   if (dt != DSV_BF16) return PartPlan{};
-  return group_part_plan(p, 0, n, pr, [](const dsv_fwd_proj& q, int32_t* o, int32_t* c) { *o = q.N, *c = q.K; });
+  return group_part_plan(p, 0, n, pr, masked, [](const dsv_fwd_proj& q, int32_t* o, int32_t* c) { *o = q.N, *c = q.K; });
 }
 PartPlan bwd_group_part(const dsv_plan& p, dsv_dtype dt, int32_t n, const dsv_bwd_proj* pr) {
   if (dt != DSV_BF16) return PartPlan{};
-  return group_part_plan(p, 1, n, pr, [](const dsv_bwd_proj& q, int32_t* o, int32_t* c) { *o = q.K, *c = q.N; });
+  return group_part_plan(p, 1, n, pr, false, [](const dsv_bwd_proj& q, int32_t* o, int32_t* c) { *o = q.K, *c = q.N; });
 }
 
 int check_common(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N) {
@@ -806,7 +829,7 @@ int fwd_impl(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N, const void* 
   //     every row.  A workspace without room for the pieces takes the tiles.  The
   //     fixed scratch of the allocation-free form has room or not for any grouping of
   //     the rows alike: its pieces need none of the other regions (no dropout there).
-  const PartPlan pp = fwd_part_plan(*p, dt, K, N, !noalloc);
+  const PartPlan pp = fwd_part_plan(*p, dt, K, N, !noalloc, dropping);
   char* parts = at<char>(workspace, noalloc ? 0 : ws.total);
   if (pp.use && (noalloc ? workspace_bytes >= pp.bytes_any : workspace_bytes - ws.total >= pp.bytes)) {
     if (keep && launch_shrink(sk, p->n_shrink, p->r_used, s) != hipSuccess) return DSV_ERR_DEVICE;
@@ -1422,7 +1445,7 @@ int fwd_grouped_impl(const dsv_plan* p, dsv_dtype dt, int32_t n_proj, const dsv_
   }
   // 1a. few rows: every base product in pieces, the shrinks beside them (a launch
   //     of their own where dropout masks them), then their sums with the low-rank terms
-  const PartPlan pp = fwd_group_part(*p, dt, n_proj, projs);
+  const PartPlan pp = fwd_group_part(*p, dt, n_proj, projs, dropping);
   if (pp.use && workspace_bytes - total >= pp.bytes) {
     if (dropping && launch_shrink_group(sg, p->n_shrink, p->r_used, s) != hipSuccess) return DSV_ERR_DEVICE;
     PartGroup pg{};

@@ -217,10 +217,10 @@ def test_wide_pieces_one_weight_transposed(T, drop):
 # T_t, K, N, projections of a masked backward whose dX has half tiles, and the tiles that
 # stay whole and the tiles halved of one launch.
 MASKED_HALVES = [
-    (3073, 1024, 4096, 2, 0, 104),   # the last row tile ends in its first half
+    (3073, 1024, 4096, 2, 0, 104),   # halves only; the last row tile ends in its first half
     (3300, 1024, 4096, 2, 0, 104),   # ... in its second
-    (2049, 2048, 2048, 1, 0, 72),    # single calls: halves only ...
-    (5000, 4104, 2048, 1, 256, 84),  # ... and behind whole tiles, the last column tile 8 wide
+    (2049, 4104, 512, 2, 256, 50),   # behind whole tiles, the last column tile 8 wide
+    (5000, 4104, 2048, 1, 256, 84),  # a single call
 ]
 
 
