@@ -587,7 +587,8 @@ __device__ __forceinline__ u32x2v ld4_sel(const uint16_t* p, int64_t stride, int
 // CLAMP: bound the descriptor's row count by the tile (half tiles need it; a whole
 // tile's is at most 256 anyway, and there it only moves the register allocation: with
 // it the grouped NN form of whole tiles spills 17 registers instead of 1 and took
-// 4-7% longer, without it the split NN form spills 133 instead of 45).
+// 4-7% longer, without it the split NN form spills 133 instead of 45 and the single NN
+// form takes 0.8% longer: only the first leaves it out).
 template <bool SK, bool DROP, bool NN, int FM, bool CLAMP = true>
 __device__ __forceinline__ void gemm_piece16(const GemmArgs& g, char* smem0, char* smem1, int tid, int lin, int t_sk,
                                              int piece,
@@ -1215,7 +1216,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     kb = (int)(((int64_t)piece * nk) / g.sk_split);
     ke = (int)(((int64_t)(piece + 1) * nk) / g.sk_split);
   }
-  gemm_piece16<SK, DROP, NN, 8, SK || HALF>(g, smem0, smem1, threadIdx.x, lin, t_sk, piece, kb, ke, nk);
+  gemm_piece16<SK, DROP, NN, 8>(g, smem0, smem1, threadIdx.x, lin, t_sk, piece, kb, ke, nk);
 }
 
 template <bool DROP, bool NN, bool HALF>
@@ -1243,7 +1244,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int local = (int)blockIdx.x - G.off[pj];
   const int lin = xcd_major(local, G.off[pj + 1] - G.off[pj]);
   const int nk = (g.C + 63) / 64;
-  gemm_piece16<false, DROP, NN, 8, HALF>(g, smem0, smem1, threadIdx.x, lin, -1, 0, 0, nk, nk);
+  gemm_piece16<false, DROP, NN, 8, HALF || DROP || !NN>(g, smem0, smem1, threadIdx.x, lin, -1, 0, 0, nk, nk);
 }
 
 // ---------------------------------------------------------------------------
