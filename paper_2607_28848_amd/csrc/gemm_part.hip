@@ -219,8 +219,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(
   const uint16_t* b_base = NN ? g.Q + n0 : g.Q + (int64_t)n0 * g.ldq;
 
   // Lane offsets of the loads: load q = wave * LA + i fills LDS rows 8q .. 8q+7,
-  // lane ln taking row 8q + ln/8, slot ln%8.  Offsets stay below 2^29 (at most
-  // 128 rows of 2^20 elements), so the out-of-range value exceeds every range.
+  // lane ln taking row 8q + ln/8, slot ln%8.  Offsets stay within 2^29
+  // bytes (at most 256 rows of 2^20 elements), so the out-of-range value exceeds them all.
   const int lr = lane >> 3;
   int off_la[LA], ch_a[LA], off_lb[LB], ch_b[LB];
 #pragma unroll
