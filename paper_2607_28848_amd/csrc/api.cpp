@@ -126,7 +126,6 @@ GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool fw
 //   and 100; K = 1024, N = 32768, 128 rows: 34 and 23, so tiles
 //   kTieUs: a small single call may lose that much by its pieces, so that its group has them
 //   kRowsMargin: above 512 rows a forward's pieces must be that much ahead
-//   kMaskedShrinkUs: a masked forward's shrink is a launch of its own
 //   kSideUs: above 2048 rows tiles hide the grouped backward's dA reduction (two K = 1024, N =
 //   3072, 3399 rows: 84 us, in pieces 100)
 // Narrow outputs take pieces at thousands of rows too (K = 2048, N = 64, 16384 training rows:
@@ -136,8 +135,9 @@ GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool fw
 // rows: 160 and 135; three K = 4096, N = 64, 16384 rows: 218 and 178); nor dX above the 32768
 // rows timed, which keeps the sum's grid of rows within 65535 however many adapters they have.
 // A forward's choice depends on the number of rows and the shapes, never on how the
-// rows are grouped into segments (the launch that gathered rows cost the tiles, about
-// 6 us, is left out for that): the base product of a row is the same bits in every
+// rows are grouped into segments or whether training rows are masked (the launch that
+// gathered rows cost the tiles, about 6 us, and the masked shrink's that pieces need, as
+// much, are left out for that): the base product of a row is the same bits in every
 // table of as many rows.
 struct PartPlan {
   bool use = false;
@@ -156,7 +156,7 @@ constexpr double kPieceStep[kPartCfgs] = {0.21, 0.47, 0.56, 0.89}, kPieceEnd[kPa
 constexpr double kPieceWeightBytesPerUs[kPartCfgs] = {6.63e6, 6.5e6, 6.59e6, 4.69e6}, kPieceElemUs = 1.87e-6;
 // what the pieces' other launches cost more than the tiles': up to 256 rows, above; forward, dX; single, grouped
 constexpr double kPieceBase[2][2][2] = {{{-1.9, -9.5}, {1.3, -10.8}}, {{-2.3, 0.7}, {-0.5, -8.7}}};
-constexpr double kMaskedShrinkUs = 5.84, kShrinkBytesPerUs = 7.16e6, kSideUs = 15.0, kTieUs[2] = {1.5, 5.0}, kRowsMargin = 1.1;
+constexpr double kShrinkBytesPerUs = 7.16e6, kSideUs = 15.0, kTieUs[2] = {1.5, 5.0}, kRowsMargin = 1.1;
 
 // Time of 256 x 256 tiles at least: the stream of their weights.
 double stream256_us(double weight_bytes, double tiles) {
@@ -177,7 +177,7 @@ double tiles_us(const GemmPlan& g, int32_t M, int32_t Nout, int32_t C) {
 }
 
 // p (forward): the plan whose shrink runs beside the pieces.
-PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout, const int32_t* C, double t_tiles, bool masked) {
+PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout, const int32_t* C, double t_tiles) {
   PartPlan best;
   const int cus = device_cus();
   if (cus <= 0 || M <= 0 || M > (p ? kFwdPartRows : kBwdPartRows)) return best;
@@ -225,7 +225,6 @@ PartPlan part_plan(const dsv_plan* p, int32_t M, int32_t n, const int32_t* Nout,
   if (t_best == HUGE_VAL) return best;
   piece_us += kPieceBase[M > 256][p == nullptr][n > 1];
   if (p) piece_us += std::min(1.0, std::max(0.0, (M - 2048) / 6144.0)) * x_bytes / kShrinkBytesPerUs;
-  if (masked) piece_us += kMaskedShrinkUs;
   if (p && M > 512) piece_us *= kRowsMargin;
   if (!p && n > 1 && M > 2048) piece_us += kSideUs;
   best.use = piece_us < t_tiles + (n == 1 && M <= 256 ? kTieUs[p == nullptr] : 0.0);
@@ -325,19 +324,19 @@ GemmPlan bwd_gemm_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
 }
 
 // Pieces or tiles of one projection's forward / dX GEMM.
-PartPlan fwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N, bool allow_split = true, bool masked = false) {
+PartPlan fwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N, bool allow_split = true) {
   if (dt != DSV_BF16 || p.T == 0) return PartPlan{};
-  return part_plan(&p, p.T, 1, &N, &K, tiles_us(fwd_gemm_plan(p, dt, K, N, allow_split), p.T, N, K), masked);
+  return part_plan(&p, p.T, 1, &N, &K, tiles_us(fwd_gemm_plan(p, dt, K, N, allow_split), p.T, N, K));
 }
 PartPlan bwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
   if (dt != DSV_BF16 || p.T_t == 0) return PartPlan{};
-  return part_plan(nullptr, p.T_t, 1, &K, &N, tiles_us(bwd_gemm_plan(p, dt, K, N), p.T_t, K, N), false);
+  return part_plan(nullptr, p.T_t, 1, &K, &N, tiles_us(bwd_gemm_plan(p, dt, K, N), p.T_t, K, N));
 }
 // ... of a grouped call, whose tiles share one launch of whole 256 x 256 tiles.
 // A projection whose single call splits no contraction keeps its whole tiles
 // (its grouped result is the single call's, bit for bit).
 template <typename Proj, typename ShapeOf>
-PartPlan group_part_plan(const dsv_plan& p, int pass, int32_t n, const Proj* pr, bool masked, ShapeOf shape) {
+PartPlan group_part_plan(const dsv_plan& p, int pass, int32_t n, const Proj* pr, ShapeOf shape) {
   const int32_t M = pass == 0 ? p.T : p.T_t, mtiles = pass == 0 ? p.n_ftiles : p.n_btiles;
   const int cus = device_cus();
   if (cus <= 0 || M == 0) return PartPlan{};
@@ -364,20 +363,20 @@ PartPlan group_part_plan(const dsv_plan& p, int pass, int32_t n, const Proj* pr,
                      kTileStep[2] * (steps + 0.5 * shortest) + kTileEnd[2] * (tiles + 0.5));
   }
   whole = std::max(whole, stream256_us(w_bytes, tiles * cus));
-  const PartPlan pp = part_plan(pass == 0 ? &p : nullptr, M, n, Nout, C, whole, masked);
+  const PartPlan pp = part_plan(pass == 0 ? &p : nullptr, M, n, Nout, C, whole);
   for (int i = 0; pp.use && i < n; ++i)
     if (!(pass == 0 ? fwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N) : bwd_gemm_plan(p, DSV_BF16, pr[i].K, pr[i].N)).sk_tiles &&
-        !(pass == 0 ? fwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N, true, masked) : bwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N)).use)
+        !(pass == 0 ? fwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N) : bwd_part_plan(p, DSV_BF16, pr[i].K, pr[i].N)).use)
       return PartPlan{};
   return pp;
 }
-PartPlan fwd_group_part(const dsv_plan& p, dsv_dtype dt, int32_t n, const dsv_fwd_proj* pr, bool masked = false) {
+PartPlan fwd_group_part(const dsv_plan& p, dsv_dtype dt, int32_t n, const dsv_fwd_proj* pr) {
   if (dt != DSV_BF16) return PartPlan{};
-  return group_part_plan(p, 0, n, pr, masked, [](const dsv_fwd_proj& q, int32_t* o, int32_t* c) { *o = q.N, *c = q.K; });
+  return group_part_plan(p, 0, n, pr, [](const dsv_fwd_proj& q, int32_t* o, int32_t* c) { *o = q.N, *c = q.K; });
 }
 PartPlan bwd_group_part(const dsv_plan& p, dsv_dtype dt, int32_t n, const dsv_bwd_proj* pr) {
   if (dt != DSV_BF16) return PartPlan{};
-  return group_part_plan(p, 1, n, pr, false, [](const dsv_bwd_proj& q, int32_t* o, int32_t* c) { *o = q.K, *c = q.N; });
+  return group_part_plan(p, 1, n, pr, [](const dsv_bwd_proj& q, int32_t* o, int32_t* c) { *o = q.K, *c = q.N; });
 }
 
 int check_common(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N) {
@@ -829,7 +828,7 @@ int fwd_impl(const dsv_plan* p, dsv_dtype dt, int32_t K, int32_t N, const void* 
   //     every row.  A workspace without room for the pieces takes the tiles.  The
   //     fixed scratch of the allocation-free form has room or not for any grouping of
   //     the rows alike: its pieces need none of the other regions (no dropout there).
-  const PartPlan pp = fwd_part_plan(*p, dt, K, N, !noalloc, dropping);
+  const PartPlan pp = fwd_part_plan(*p, dt, K, N, !noalloc);
   char* parts = at<char>(workspace, noalloc ? 0 : ws.total);
   if (pp.use && (noalloc ? workspace_bytes >= pp.bytes_any : workspace_bytes - ws.total >= pp.bytes)) {
     if (keep && launch_shrink(sk, p->n_shrink, p->r_used, s) != hipSuccess) return DSV_ERR_DEVICE;
@@ -1445,7 +1444,7 @@ int fwd_grouped_impl(const dsv_plan* p, dsv_dtype dt, int32_t n_proj, const dsv_
   }
   // 1a. few rows: every base product in pieces, the shrinks beside them (a launch
   //     of their own where dropout masks them), then their sums with the low-rank terms
-  const PartPlan pp = fwd_group_part(*p, dt, n_proj, projs, dropping);
+  const PartPlan pp = fwd_group_part(*p, dt, n_proj, projs);
   if (pp.use && workspace_bytes - total >= pp.bytes) {
     if (dropping && launch_shrink_group(sg, p->n_shrink, p->r_used, s) != hipSuccess) return DSV_ERR_DEVICE;
     PartGroup pg{};

@@ -58,9 +58,12 @@ class Recorded:
     def noalloc(self, p, K, N):
         return self.call(self.lib.dsv_cobatch_fwd_noalloc, p.handle, 0, K, N, BUF, BUF, BUF, BUF, BUF, BUF, None)
 
-    def fwd_grouped(self, p, shapes):
+    def fwd_grouped(self, p, shapes, dropout=False):
         n = self.dsv.fwd_grouped_workspace_bytes(p, 0, shapes)
         pr = b"".join(self.dsv._FWD_PACK(K, N, BUF, BUF, BUF, BUF, BUF, BUF, 0, 0, 0) for K, N in shapes)
+        if dropout:
+            drops = (self.dsv.Dropout * len(shapes))(*[self.dsv.Dropout(0.05, 1, i, None) for i in range(len(shapes))])
+            return self.call(self.lib.dsv_cobatch_fwd_grouped_dropout, p.handle, 0, len(shapes), pr, drops, WS, n, None)
         return self.call(self.lib.dsv_cobatch_fwd_grouped, p.handle, 0, len(shapes), pr, WS, n, None)
 
     def bwd_grouped(self, p, shapes, wt=True, dropout=False, short=0):
@@ -93,7 +96,8 @@ def _base(launches):
 @pytest.mark.parametrize("K,N", [(4096, 4096), (4096, 14336), (14336, 4096), (1024, 1024), (520, 776)])
 def test_base_product_does_not_depend_on_the_grouping(rec, K, N):
     """Tables of as many rows, one segment or every row on its own (all gathered), sum the
-    base product alike in every forward: with B = 0 their results are then the same bits."""
+    base product alike in every forward, masked training rows or none: with B = 0 their
+    results are then the same bits."""
     refused = 0
     for T in list(range(1, 258, 37)) + list(range(260, 1400, 29)):
         a = rec.plan([(0, T, 0, 0)], [16, 16], 16)
@@ -107,6 +111,9 @@ def test_base_product_does_not_depend_on_the_grouping(rec, K, N):
                 continue
             assert ra == rb == rec.dsv.OK
             assert _base(la) and _base(la) == _base(lb), (what, T, la, lb)
+        c = rec.plan([(0, T - T // 2, 0, 0), (T - T // 2, T // 2, 1, 1)], [16, 16], 16)
+        for shapes in ([(K, N)], [(K, N), (K, 8 * (N // 16))]):
+            assert _base(rec.fwd_grouped(c, shapes, dropout=True)[1]) == _base(rec.fwd_grouped(a, shapes)[1])
     assert refused < 40
 
 
