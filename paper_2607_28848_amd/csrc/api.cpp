@@ -49,9 +49,9 @@ int device_cus() {
 //     low-rank term of the 128 x 128 form keeps a NaN in its own column, that of
 //     the 256 x 256 form does not.  Not a forward whose only wave is split in two:
 //     about 120 to 146 K-steps by the costs above, over which the split form gains more
-//     per K-step than its sum costs (1007 x 9016 x 5880: 131 us, 161 in halves; 69
-//     such calls: halves 9% longer on average).  dX keeps halves there: W as it is
-//     gains 6% by them (W transposed loses 9%, and both must give the same bits).
+//     per K-step than its sum costs (1007 x 9016 x 5880: 131 us, 161 in halves; 69 such
+//     calls: halves 9% longer in the mean).  dX keeps halves there: split in two, 58 such dX
+//     took 4% longer with W as it is and 4% less transposed, and both must give the same bits.
 // The constants were fitted to timings of the Llama-3-8B projections
 // (forward and dX) on MI355X.
 struct GemmPlan {
@@ -115,7 +115,7 @@ GemmPlan plan_gemm(int32_t m256, int32_t m128, int32_t n_out, int32_t C, bool fw
 // forward and dX, masked and not, 1 .. 8192 rows, 8 .. 28672 columns, Llama shapes, random
 // ones, and tables of decode, prefill and training segments:
 //   tiles    kTileStep per K-step and kTileEnd per round of the form (kHalfStep, kHalfEnd
-//            for half tiles; a split round and its sum: kSplitSum and the fp32 pieces at
+//            for half tiles, forward and dX; a split round and its sum: kSplitSum and the fp32 pieces at
 //            5 TB/s more), at least the stream of the weights
 //   pieces   kPieceStep per K-step of a piece and kPieceEnd per round, at least the stream
 //            of the weights; kPieceElemUs per fp32 element of the pieces; kPieceBase
@@ -151,7 +151,7 @@ constexpr int kMinPartSteps = 4, kFwdPartRows = 8192, kBwdPartRows = 32768;
 constexpr double kPartBytesPerUs = 5e6, kWeightBytesPerUs = 5.5e6;
 // 128 x 128 tiles with one workgroup per CU, with two, 256 x 256 tiles
 constexpr double kTileStep[3] = {0.68, 0.76, 1.37}, kTileEnd[3] = {0.27, 4.53, 5.72}, kTileWeightBytesPerUs[3] = {3.47e6, 5.2e6, 5.05e6};
-constexpr double kOneTileBytesPerUs = 0.129e6, kHalfStep = 1.08, kHalfStepRows128 = 1.18, kHalfEnd = 5.23, kSplitSum = 11.2, kSplitBytesPerUs = 5.02e6;
+constexpr double kOneTileBytesPerUs = 0.129e6, kHalfStep[2] = {1.08, 0.9}, kHalfStepRows128 = 1.18, kHalfEnd = 5.23, kSplitSum = 11.2, kSplitBytesPerUs = 5.02e6;
 constexpr double kPieceStep[kPartCfgs] = {0.21, 0.47, 0.56, 0.89}, kPieceEnd[kPartCfgs] = {0.01, 0.63, 1.54, 0.42};
 constexpr double kPieceWeightBytesPerUs[kPartCfgs] = {6.63e6, 6.5e6, 6.59e6, 4.69e6}, kPieceElemUs = 1.87e-6;
 // what the pieces' other launches cost more than the tiles': up to 256 rows, above; forward, dX; single, grouped
@@ -162,14 +162,14 @@ constexpr double kShrinkBytesPerUs = 7.16e6, kSideUs = 15.0, kTieUs[2] = {1.5, 5
 double stream256_us(double weight_bytes, double tiles) {
   return weight_bytes / std::min(kTileWeightBytesPerUs[2], kOneTileBytesPerUs * tiles);
 }
-double half_us(int32_t M, double nk) { return (M <= 128 ? kHalfStepRows128 : kHalfStep) * nk + kHalfEnd; }
-double tiles_us(const GemmPlan& g, int32_t M, int32_t Nout, int32_t C) {
+double half_us(bool fwd, int32_t M, double nk) { return (M <= 128 ? kHalfStepRows128 : kHalfStep[!fwd]) * nk + kHalfEnd; }
+double tiles_us(bool fwd, const GemmPlan& g, int32_t M, int32_t Nout, int32_t C) {
   const int64_t cus = device_cus(), nk = (C + 63) / 64;
   if (cus <= 0) return 0.0;  // no device: no launch plan either
   const int form = g.tm == 256 ? 2 : g.dp_tiles <= cus ? 0 : 1;
   const int64_t per = form == 1 ? 2 * cus : cus;
   double t = (double)((g.dp_tiles + per - 1) / per) * (kTileStep[form] * nk + kTileEnd[form]);
-  if (g.half_tiles > 0) t += half_us(M, nk);
+  if (g.half_tiles > 0) t += half_us(fwd, M, nk);
   if (g.sk_tiles > 0)
     t += kTileStep[2] * nk / g.sk_split + kSplitSum + (double)g.sk_tiles * g.sk_split * g.tm * g.tn * 8 / kSplitBytesPerUs;
   const double w_bytes = 2.0 * Nout * C;
@@ -326,11 +326,11 @@ GemmPlan bwd_gemm_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
 // Pieces or tiles of one projection's forward / dX GEMM.
 PartPlan fwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N, bool allow_split = true) {
   if (dt != DSV_BF16 || p.T == 0) return PartPlan{};
-  return part_plan(&p, p.T, 1, &N, &K, tiles_us(fwd_gemm_plan(p, dt, K, N, allow_split), p.T, N, K));
+  return part_plan(&p, p.T, 1, &N, &K, tiles_us(true, fwd_gemm_plan(p, dt, K, N, allow_split), p.T, N, K));
 }
 PartPlan bwd_part_plan(const dsv_plan& p, dsv_dtype dt, int32_t K, int32_t N) {
   if (dt != DSV_BF16 || p.T_t == 0) return PartPlan{};
-  return part_plan(nullptr, p.T_t, 1, &K, &N, tiles_us(bwd_gemm_plan(p, dt, K, N), p.T_t, K, N));
+  return part_plan(nullptr, p.T_t, 1, &K, &N, tiles_us(false, bwd_gemm_plan(p, dt, K, N), p.T_t, K, N));
 }
 // ... of a grouped call, whose tiles share one launch of whole 256 x 256 tiles.
 // A projection whose single call splits no contraction keeps its whole tiles
@@ -357,7 +357,7 @@ PartPlan group_part_plan(const dsv_plan& p, int pass, int32_t n, const Proj* pr,
   if (shortest == longest) {  // rounds over the CUs, the last one of halves where they fit
     const double part = tiles - std::floor(tiles);
     whole = (std::floor(tiles) + (part > 0.5 ? 1.0 : 0.0)) * round(longest);
-    if (part > 0.0 && part <= 0.5) whole += half_us(M, longest);
+    if (part > 0.0 && part <= 0.5) whole += half_us(pass == 0, M, longest);
   } else {  // the shorter ones fill up behind the longest
     whole = std::max(std::ceil(long_tiles / cus) * round(longest),
                      kTileStep[2] * (steps + 0.5 * shortest) + kTileEnd[2] * (tiles + 0.5));

@@ -256,3 +256,23 @@ def test_masked_half_tiles(Tt, K, N, n, whole, halves, wt):
     err = oracle.rel_err(to_host(got[0][2])[rows], dXr)
     print("  dX %.2e" % err, flush=True)
     assert err <= TOL_BF16
+
+
+def test_one_wave_of_dx_same_bits_either_weight():
+    """dX of 1007 rows over 141 K-steps, 92 tiles in halves: W as it is and transposed give
+    the same bits, within the bar on rows at the tiles' edges."""
+    import torch
+    from paper_2607_28848_amd import dsv
+    Tt, K, N = 1007, 5880, 9016
+    w = wl.custom([(0, 300, 0, 1), (300, Tt - 300, 1, 1)], [16, 8], K=K, N=N, r_max=16, name="one_wave")
+    t = w.tensors(0, pad=np.nan)
+    d = {k: to_dev(t.store[k], "bf16") for k in ("X", "W", "A", "B", "dY")}
+    plan = dsv.segments_build(w.segments, w.n_tokens, w.ranks, w.scales, w.r_max, device="cuda")
+    c = dsv.gemm_config(plan, dsv.BF16, K, N, 1)
+    print("dX %s" % c, flush=True)
+    out = [dsv.lora_bwd_grouped(plan, [(d["X"], d["W"], d["A"], d["B"], None, d["dY"])], wts=wts)[0][2]
+           for wts in (None, [d["W"].t().contiguous()])]
+    torch.cuda.synchronize()
+    assert torch.equal(_bits(out[0]), _bits(out[1]))
+    rows = np.array([0, 127, 128, 255, 256, 299, 300, 767, 768, 1006], dtype=np.int32)
+    assert oracle.rel_err(to_host(out[0])[rows], oracle_bwd(w, t, dx_rows=rows)[3]) <= TOL_BF16

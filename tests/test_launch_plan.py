@@ -175,6 +175,17 @@ def test_one_wave_over_a_long_contraction_is_split(rec, T, K, N):
     assert rc == rec.dsv.OK and l["kind"] == "gemm_nt" and (l["split"], l["pieces"], l["half"]) == (l["tiles"], 2, 0)
 
 
+@pytest.mark.parametrize("Tt,K,N", [(1007, 5880, 9016), (6498, 840, 8224), (2337, 2424, 8104)])
+def test_one_wave_of_dx_is_halved_either_way(rec, Tt, K, N):
+    """dX of one partial wave over about 130 K-steps: half tiles with W as it is and transposed,
+    which must give the same bits, and no pieces (timed in 163 .. 284 us, halves 141 .. 177)."""
+    for wt in (False, True):
+        rc, launches = rec.bwd_grouped(rec.plan([(0, Tt, 0, 1)], [16], 16), [(K, N)], wt=wt)
+        l, = [l for l in launches if re.match("part|gemm", l["kind"])]
+        assert rc == rec.dsv.OK and l["kind"] == ("gemm_nt" if wt else "gemm_nn")
+        assert (l["split"], l["half"]) == (0, l["tiles"])
+
+
 @pytest.mark.parametrize("T", [8192, 8193, 32768, 32769, 70000])
 def test_rows_of_the_sum_fit_its_grid(rec, T):
     """Every row with an adapter of its own: the sum has a row of workgroups for each 16 rows of
